@@ -438,7 +438,7 @@ SPARCML_API int sparcml_densify(const sparcml_stream* in, uint64_t N, float* den
  */
 #define SPARCML_TIMER_REDUCE_PASS 0  /* first tile pass of sparse_reduce */
 #define SPARCML_TIMER_REDUCE_WRITE 1 /* sparse-output tile pass */
-#define SPARCML_TIMER_REDUCE_SLOW 2  /* pass over tiles too full for the first pass */
+#define SPARCML_TIMER_REDUCE_SLOW 2  /* node sizes after a dense pass without them */
 #define SPARCML_TIMER_QUANT_NORM 3   /* QSGD norm partials */
 #define SPARCML_TIMER_QUANT_CODES 4  /* QSGD coding */
 #define SPARCML_TIMER_TOPK_SELECT 5  /* top-k radix-select histogram passes */

@@ -42,7 +42,7 @@ struct DescArgs {
 enum TimerSlot {
     kTReducePass = 0,   // first tile pass of sparse_reduce (count or dense)
     kTReduceWrite = 1,  // sparse-output tile pass
-    kTReduceSlow = 2,   // deferred-tile pass following the first tile pass
+    kTReduceSlow = 2,   // counting pass of the node sizes after a dense pass without them
     kTQuantNorm = 3,    // QSGD norm partials
     kTQuantCodes = 4,   // QSGD coding pass
     kTTopkSelect = 5,   // top-k histogram passes
@@ -109,7 +109,8 @@ struct Carve {
 // ---------------------------------------------------------------- reduce
 // The reduction covers the index range [lo, lo + N); stream indices lie in it.
 struct ReducePlan {
-    uint32_t P, L, PK, T, ntiles, nchunks, tiles_per_chunk, qbits;  // PK: rank class 16/32/64/128/256
+    uint32_t P, L, nchunks, qbits;
+    uint64_t chunk;  // indices per chunk of the tile pass
     uint64_t N, lo, thr, sum_nnz, max_nnz;
     int speculate_dense;
     int small;  // few slots, every node sparse, few entries: the one-workgroup merge tree
