@@ -23,20 +23,20 @@ struct QDesc {
     uint64_t n;
 };
 
-// Stream r's descriptor: from the launch's arguments (ARGS: six words a
-// stream, val, q and n; no dequantized copy), else from the uploaded table.
+// Stream r's descriptor: from the launch's arguments (ARGS words a stream: six,
+// val, q and n, or eight, deq too), else (ARGS = 0) from the uploaded table.
 // (A template parameter: chosen at run time, the two sources were merged by
 // the compiler into one generic pointer and a vector load per workgroup;
 // each instantiation now reads its own source with scalar loads.)
-template <bool ARGS>
+template <int ARGS>
 __device__ __forceinline__ QDesc qdesc(const QDesc* tab, const Blob& tb, uint32_t r)
 {
-    if (!ARGS) return tab[r];
-    const uint32_t* w = tb.words + 6u * r;
+    if (ARGS == 0) return tab[r];
+    const uint32_t* w = tb.words + (uint32_t)ARGS * r;
     QDesc d;
     d.val = reinterpret_cast<const float*>((uint64_t)w[0] | (uint64_t)w[1] << 32);
     d.q = reinterpret_cast<uint8_t*>((uint64_t)w[2] | (uint64_t)w[3] << 32);
-    d.deq = nullptr;
+    d.deq = ARGS == 8 ? reinterpret_cast<float*>((uint64_t)w[6] | (uint64_t)w[7] << 32) : nullptr;
     d.n = (uint64_t)w[4] | (uint64_t)w[5] << 32;
     return d;
 }
@@ -89,7 +89,7 @@ __device__ __forceinline__ double wave_sumsq(const float* v, uint64_t n, uint64_
 // stream r (zeros past the end), a wave per 2048 elements and the four
 // wave sums pairwise; with one block a stream (scale non-null) that is the
 // norm^2, and scale[r] = its square root.
-template <bool ARGS>
+template <int ARGS>
 __global__ void __launch_bounds__(256) k_sumsq_partial(const QDesc* tab, Blob tb, double* partial, uint32_t Q,
                                                        float* scale)
 {
@@ -152,20 +152,28 @@ __device__ __forceinline__ uint4 philox(uint4 c, uint32_t k0, uint32_t k1)
     return c;
 }
 
-// Elements e0 .. e0 + 32/BITS - 1 of stream r quantized into one 32-bit
-// word of codes (4 elements per Philox block), the dequantized values
-// stored too when the stream asks for them.
-template <int BITS>
-__device__ __forceinline__ void quant_word(const QDesc& d, uint32_t r, uint64_t e0, float scale, uint32_t k0,
-                                           uint32_t k1)
+// Four dequantized values from element e on, those below n: one store where
+// all are there and aligned (four scattered words a lane fill a line in four
+// partial writes).  With this, a thread's four words (kWords) and the
+// descriptors in the launch's arguments, 8 ragged streams of 2.4 to 3.1 M
+// with 8-bit codes and copies take 64.8 us instead of 77.3 (210 MB at least;
+// bound by two passes over the values and the launches between them).
+__device__ __forceinline__ void put_deq(float* deq, uint64_t e, uint64_t n, const float* v)
 {
-    constexpr int EPT = 32 / BITS;
-    constexpr uint32_t S = (1u << (BITS - 1)) - 1u;
-    const float inv = scale > 0.0f ? __fdiv_rn((float)S, scale) : 0.0f;
-    const float unit = __fdiv_rn(scale, (float)S);
-    float x[EPT];
-    const bool full = e0 + EPT <= d.n;
-    if (full && ((reinterpret_cast<uintptr_t>(d.val + e0) & 15u) == 0)) {
+    if (e + 4u <= n && (reinterpret_cast<uintptr_t>(deq + e) & 15u) == 0u) {
+        *reinterpret_cast<float4*>(deq + e) = make_float4(v[0], v[1], v[2], v[3]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (e + i < n) deq[e + i] = v[i];
+    }
+}
+
+// EPT values from element e0 on (zeros past n).
+template <int EPT>
+__device__ __forceinline__ void load_word(const QDesc& d, uint64_t e0, float* x)
+{
+    if (e0 + EPT <= d.n && ((reinterpret_cast<uintptr_t>(d.val + e0) & 15u) == 0)) {
 #pragma unroll
         for (int i = 0; i < EPT; i += 4) {
             const float4 t = *reinterpret_cast<const float4*>(d.val + e0 + i);
@@ -178,12 +186,26 @@ __device__ __forceinline__ void quant_word(const QDesc& d, uint32_t r, uint64_t 
 #pragma unroll
         for (int i = 0; i < EPT; ++i) x[i] = e0 + i < d.n ? d.val[e0 + i] : 0.0f;
     }
+}
+
+// Elements e0 .. e0 + 32/BITS - 1 of stream r, x, quantized into one 32-bit
+// word of codes (4 elements per Philox block), the dequantized values
+// stored too when the stream asks for them.
+template <int BITS>
+__device__ __forceinline__ void quant_word(const QDesc& d, uint32_t r, uint64_t e0, const float* x, float scale,
+                                           uint32_t k0, uint32_t k1)
+{
+    constexpr int EPT = 32 / BITS;
+    constexpr uint32_t S = (1u << (BITS - 1)) - 1u;
+    const float inv = scale > 0.0f ? __fdiv_rn((float)S, scale) : 0.0f;
+    const float unit = __fdiv_rn(scale, (float)S);
     uint32_t word = 0;
 #pragma unroll
     for (int g = 0; g < EPT; g += 4) {
         const uint64_t blk = (e0 + g) >> 2;
         const uint4 w4 = philox(make_uint4((uint32_t)blk, r, 0u, 0u), k0, k1);
         const uint32_t wr[4] = {w4.x, w4.y, w4.z, w4.w};
+        float dq[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int ii = g + i;
@@ -199,11 +221,10 @@ __device__ __forceinline__ void quant_word(const QDesc& d, uint32_t r, uint64_t 
             const uint32_t sign = (x[ii] < 0.0f && l > 0u) ? 1u : 0u;
             const uint32_t code = (sign << (BITS - 1)) | l;
             word |= code << (ii * BITS);
-            if (d.deq && e0 + ii < d.n) {
-                const float mag = __fmul_rn((float)l, unit);
-                d.deq[e0 + ii] = l == 0u ? 0.0f : (sign ? -mag : mag);
-            }
+            const float mag = __fmul_rn((float)l, unit);
+            dq[i] = l == 0u ? 0.0f : (sign ? -mag : mag);
         }
+        if (d.deq) put_deq(d.deq, e0 + g, d.n, dq);
     }
     const uint64_t byte0 = e0 * BITS / 8;
     const uint64_t nbytes = (d.n * BITS + 7) / 8;
@@ -215,17 +236,30 @@ __device__ __forceinline__ void quant_word(const QDesc& d, uint32_t r, uint64_t 
     }
 }
 
-// Each thread quantizes 32/bits consecutive elements into one word.
-template <int BITS, bool ARGS>
+// Each thread quantizes 32/bits consecutive elements into one word; with
+// 8-bit codes, where these are one 16-byte load, kWords words 256 apart whose
+// loads are in flight together.
+template <int BITS>
+constexpr int kWords = BITS == 8 ? 4 : 1;
+
+template <int BITS, int ARGS>
 __global__ void __launch_bounds__(256) k_quantize(const QDesc* tab, Blob tb, const float* scales, uint32_t k0,
                                                   uint32_t k1)
 {
-    constexpr int EPT = 32 / BITS;
+    constexpr int EPT = 32 / BITS, W = kWords<BITS>;
     const uint32_t r = blockIdx.y;
     const QDesc d = qdesc<ARGS>(tab, tb, r);
-    const uint64_t e0 = ((uint64_t)blockIdx.x * 256 + threadIdx.x) * EPT;
+    const uint64_t e0 = ((uint64_t)blockIdx.x * (256 * W) + threadIdx.x) * EPT;
     if (e0 >= d.n) return;
-    quant_word<BITS>(d, r, e0, scales[r], k0, k1);
+    const float scale = scales[r];
+    float x[W][EPT];
+#pragma unroll
+    for (int w = 0; w < W; ++w) load_word<EPT>(d, e0 + (uint64_t)w * 256 * EPT, x[w]);
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const uint64_t e = e0 + (uint64_t)w * 256 * EPT;
+        if (e < d.n) quant_word<BITS>(d, r, e, x[w], scale, k0, k1);
+    }
 }
 
 // Streams of at most kSmallQ elements: one 1024-thread workgroup a stream
@@ -236,7 +270,7 @@ __global__ void __launch_bounds__(256) k_quantize(const QDesc* tab, Blob tb, con
 // the stream as k_quantize does (its values read again, now from the cache).
 constexpr uint64_t kSmallQ = 4 * kSeg;
 
-template <int BITS, bool ARGS>
+template <int BITS, int ARGS>
 __global__ void __launch_bounds__(1024) k_quant_small(const QDesc* tab, Blob tb, float* scales, uint32_t k0,
                                                       uint32_t k1)
 {
@@ -259,8 +293,11 @@ __global__ void __launch_bounds__(1024) k_quant_small(const QDesc* tab, Blob tb,
     }
     __syncthreads();
     const float scale = s_scale;
-    for (uint64_t e0 = (uint64_t)threadIdx.x * EPT; e0 < d.n; e0 += 1024u * EPT)
-        quant_word<BITS>(d, r, e0, scale, k0, k1);
+    for (uint64_t e0 = (uint64_t)threadIdx.x * EPT; e0 < d.n; e0 += 1024u * EPT) {
+        float x[EPT];
+        load_word<EPT>(d, e0, x);
+        quant_word<BITS>(d, r, e0, x, scale, k0, k1);
+    }
 }
 
 // Bucketed QSGD in one pass: a bucket of B (a power of two, 4..8192)
@@ -336,6 +373,7 @@ __global__ void __launch_bounds__(256) k_quantize_buckets(const QBDesc* tab, flo
     for (int g = 0; g < EPT; g += 4) {
         const uint4 w4 = philox(make_uint4((uint32_t)((e0 + g) >> 2), r, 0u, 0u), k0, k1);
         const uint32_t wr[4] = {w4.x, w4.y, w4.z, w4.w};
+        float dq[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int ii = g + i;
@@ -351,11 +389,10 @@ __global__ void __launch_bounds__(256) k_quantize_buckets(const QBDesc* tab, flo
             const uint32_t sign = (x[ii] < 0.0f && l > 0u) ? 1u : 0u;
             const uint32_t code = (sign << (BITS - 1)) | l;
             word[(ii * BITS) / 32] |= code << ((ii * BITS) % 32);
-            if (d.deq && e0 + ii < d.n) {
-                const float mag = __fmul_rn((float)l, unit);
-                d.deq[e0 + ii] = l == 0u ? 0.0f : (sign ? -mag : mag);
-            }
+            const float mag = __fmul_rn((float)l, unit);
+            dq[i] = l == 0u ? 0.0f : (sign ? -mag : mag);
         }
+        if (d.deq) put_deq(d.deq, e0 + g, d.n, dq);
     }
     // EPT * BITS / 8 bytes of codes at byte e0 * BITS / 8
     constexpr int NB = EPT * BITS / 8;
@@ -455,22 +492,28 @@ hipError_t quant_run(int P, const float* const* vals, const uint64_t* n, int bit
     uint64_t max_n = 0;
     for (int r = 0; r < P; ++r) max_n = std::max(max_n, n[r]);
     const QLayout l = qlayout(P, max_n, ws);
-    // the descriptor table: in both launches' arguments when it fits there
-    // (no dequantized copies), else uploaded first
+    // the descriptor table: in both launches' arguments when it fits there,
+    // else uploaded first
     Blob tb;
     tb.nwords = 0;
     hipError_t e = hipSuccess;
-    if (!out_deq && 6u * (uint32_t)P <= (uint32_t)kBlobWords) {
-        tb.nwords = 6u * (uint32_t)P;
+    const uint32_t args = out_deq ? 8u : 6u;
+    if (args * (uint32_t)P <= (uint32_t)kBlobWords) {
+        tb.nwords = args * (uint32_t)P;
         for (int r = 0; r < P; ++r) {
             const uint64_t a = reinterpret_cast<uint64_t>(vals[r]), b = reinterpret_cast<uint64_t>(out_q[r]);
-            uint32_t* w = tb.words + 6 * r;
+            uint32_t* w = tb.words + args * (uint32_t)r;
             w[0] = (uint32_t)a;
             w[1] = (uint32_t)(a >> 32);
             w[2] = (uint32_t)b;
             w[3] = (uint32_t)(b >> 32);
             w[4] = (uint32_t)n[r];
             w[5] = (uint32_t)(n[r] >> 32);
+            if (out_deq) {
+                const uint64_t c = reinterpret_cast<uint64_t>(out_deq[r]);
+                w[6] = (uint32_t)c;
+                w[7] = (uint32_t)(c >> 32);
+            }
         }
     } else {
         QDesc* host = new QDesc[P];
@@ -482,48 +525,34 @@ hipError_t quant_run(int P, const float* const* vals, const uint64_t* n, int bit
     }
 
     const uint32_t k0 = (uint32_t)(seed & 0xFFFFFFFFu), k1 = (uint32_t)(seed >> 32);
+    auto pick = [&](auto table, auto six, auto eight) { return !tb.nwords ? table : (args == 6u ? six : eight); };
     if (max_n > 0 && max_n <= kSmallQ) {  // short streams: norm and codes in one launch
         timer_begin(kTQuantCodes, s);
-        const dim3 g((uint32_t)P), blk(1024);
-        if (tb.nwords) {
-            if (bits == 2) hipLaunchKernelGGL((k_quant_small<2, true>), g, blk, 0, s, l.tab, tb, out_scale, k0, k1);
-            else if (bits == 4) hipLaunchKernelGGL((k_quant_small<4, true>), g, blk, 0, s, l.tab, tb, out_scale, k0, k1);
-            else hipLaunchKernelGGL((k_quant_small<8, true>), g, blk, 0, s, l.tab, tb, out_scale, k0, k1);
-        } else {
-            if (bits == 2) hipLaunchKernelGGL((k_quant_small<2, false>), g, blk, 0, s, l.tab, tb, out_scale, k0, k1);
-            else if (bits == 4) hipLaunchKernelGGL((k_quant_small<4, false>), g, blk, 0, s, l.tab, tb, out_scale, k0, k1);
-            else hipLaunchKernelGGL((k_quant_small<8, false>), g, blk, 0, s, l.tab, tb, out_scale, k0, k1);
-        }
+        const auto small = bits == 2 ? pick(k_quant_small<2, 0>, k_quant_small<2, 6>, k_quant_small<2, 8>)
+                           : bits == 4 ? pick(k_quant_small<4, 0>, k_quant_small<4, 6>, k_quant_small<4, 8>)
+                                       : pick(k_quant_small<8, 0>, k_quant_small<8, 6>, k_quant_small<8, 8>);
+        hipLaunchKernelGGL(small, dim3((uint32_t)P), dim3(1024), 0, s, l.tab, tb, out_scale, k0, k1);
         timer_end(kTQuantCodes, s);
         return hipGetLastError();
     }
     // norms; the launch that finishes a stream's norm also writes its scale
     timer_begin(kTQuantNorm, s);
     float* const scale0 = l.levels == 0 ? out_scale : nullptr;
-    if (tb.nwords)
-        hipLaunchKernelGGL(k_sumsq_partial<true>, dim3(l.count[0], P), dim3(256), 0, s, l.tab, tb, l.part[0],
-                           l.count[0], scale0);
-    else
-        hipLaunchKernelGGL(k_sumsq_partial<false>, dim3(l.count[0], P), dim3(256), 0, s, l.tab, tb, l.part[0],
-                           l.count[0], scale0);
+    hipLaunchKernelGGL(pick(k_sumsq_partial<0>, k_sumsq_partial<6>, k_sumsq_partial<8>), dim3(l.count[0], P), dim3(256),
+                       0, s, l.tab, tb, l.part[0], l.count[0], scale0);
     timer_end(kTQuantNorm, s);
     for (int lv = 1; lv <= l.levels; ++lv)
         hipLaunchKernelGGL(k_sum_f64, dim3(l.count[lv], P), dim3(1024), 0, s, l.part[lv - 1],
                            l.count[lv - 1], l.part[lv], l.count[lv], lv == l.levels ? out_scale : nullptr);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (max_n == 0) return hipSuccess;
-    const uint64_t per_block = 256ull * (32 / bits);
+    const uint64_t per_block = 256ull * (32 / bits) * (bits == 8 ? kWords<8> : bits == 4 ? kWords<4> : kWords<2>);
     const dim3 grid((uint32_t)((max_n + per_block - 1) / per_block), P);
+    const auto codes = bits == 2 ? pick(k_quantize<2, 0>, k_quantize<2, 6>, k_quantize<2, 8>)
+                       : bits == 4 ? pick(k_quantize<4, 0>, k_quantize<4, 6>, k_quantize<4, 8>)
+                                   : pick(k_quantize<8, 0>, k_quantize<8, 6>, k_quantize<8, 8>);
     timer_begin(kTQuantCodes, s);
-    if (tb.nwords) {
-        if (bits == 2) hipLaunchKernelGGL((k_quantize<2, true>), grid, dim3(256), 0, s, l.tab, tb, out_scale, k0, k1);
-        else if (bits == 4) hipLaunchKernelGGL((k_quantize<4, true>), grid, dim3(256), 0, s, l.tab, tb, out_scale, k0, k1);
-        else hipLaunchKernelGGL((k_quantize<8, true>), grid, dim3(256), 0, s, l.tab, tb, out_scale, k0, k1);
-    } else {
-        if (bits == 2) hipLaunchKernelGGL((k_quantize<2, false>), grid, dim3(256), 0, s, l.tab, tb, out_scale, k0, k1);
-        else if (bits == 4) hipLaunchKernelGGL((k_quantize<4, false>), grid, dim3(256), 0, s, l.tab, tb, out_scale, k0, k1);
-        else hipLaunchKernelGGL((k_quantize<8, false>), grid, dim3(256), 0, s, l.tab, tb, out_scale, k0, k1);
-    }
+    hipLaunchKernelGGL(codes, grid, dim3(256), 0, s, l.tab, tb, out_scale, k0, k1);
     timer_end(kTQuantCodes, s);
     return hipGetLastError();
 }

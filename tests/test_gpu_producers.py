@@ -152,8 +152,8 @@ def test_quantize_parity(bits):
     vals.append(np.float32(3.0) * np.ones(5, np.float32))
     seed = 0xDEADBEEF_12345678 + bits
     o = oracle.quantize(vals, bits, seed)
-    # with dequantized copies the table is uploaded; without, it travels in
-    # the kernels' arguments
+    # the descriptor table travels in the kernels' arguments, with and without
+    # the dequantized copies
     for want_deq in (True, False):
         say(f"[quant] bits={bits} streams={len(vals)} deq={want_deq}")
         g = gpu_quantize(vals, bits, seed, want_deq)
