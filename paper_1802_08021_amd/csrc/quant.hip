@@ -10,6 +10,8 @@
 #include "internal.h"
 
 #include <algorithm>
+#include <cstring>
+#include <type_traits>
 
 namespace sparcml {
 namespace {
@@ -314,15 +316,27 @@ struct QBDesc {
     uint64_t n;
     uint64_t soff;  // index of the stream's first scale
 };
+constexpr uint32_t kQBWords = sizeof(QBDesc) / 4;
 
-template <int BITS, int EPT>
-__global__ void __launch_bounds__(256) k_quantize_buckets(const QBDesc* tab, float* scales, uint32_t B,
+template <int BITS, int EPT, bool ARGS>
+__global__ void __launch_bounds__(256) k_quantize_buckets(const QBDesc* tab, Blob tb, float* scales, uint32_t B,
                                                           uint32_t k0, uint32_t k1)
 {
     constexpr uint32_t S = (1u << (BITS - 1)) - 1u;
     __shared__ double s_w[4];
     const uint32_t r = blockIdx.y;
-    const QBDesc d = tab[r];
+    QBDesc d;
+    if (ARGS) {  // five words of 64 bits a stream
+        const uint32_t* w = tb.words + kQBWords * r;
+        auto u64 = [&](int i) { return (uint64_t)w[2 * i] | (uint64_t)w[2 * i + 1] << 32; };
+        d.val = reinterpret_cast<const float*>(u64(0));
+        d.q = reinterpret_cast<uint8_t*>(u64(1));
+        d.deq = reinterpret_cast<float*>(u64(2));
+        d.n = u64(3);
+        d.soff = u64(4);
+    } else {
+        d = tab[r];
+    }
     const uint64_t blk0 = (uint64_t)blockIdx.x * 256 * EPT;
     if (blk0 >= d.n) return;  // uniform over the block
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -440,16 +454,15 @@ QLayout qlayout(int P, uint64_t max_n, void* ws)
     return l;
 }
 
-template <int BITS>
-void launch_buckets(dim3 grid, int ept, hipStream_t s, const QBDesc* tab, float* scales, uint32_t B,
+template <int BITS, bool ARGS>
+void launch_buckets(dim3 grid, int ept, hipStream_t s, const QBDesc* tab, const Blob& tb, float* scales, uint32_t B,
                     uint32_t k0, uint32_t k1)
 {
-    switch (ept) {
-    case 4: hipLaunchKernelGGL((k_quantize_buckets<BITS, 4>), grid, dim3(256), 0, s, tab, scales, B, k0, k1); break;
-    case 8: hipLaunchKernelGGL((k_quantize_buckets<BITS, 8>), grid, dim3(256), 0, s, tab, scales, B, k0, k1); break;
-    case 16: hipLaunchKernelGGL((k_quantize_buckets<BITS, 16>), grid, dim3(256), 0, s, tab, scales, B, k0, k1); break;
-    default: hipLaunchKernelGGL((k_quantize_buckets<BITS, 32>), grid, dim3(256), 0, s, tab, scales, B, k0, k1); break;
-    }
+    const auto k = ept == 4    ? k_quantize_buckets<BITS, 4, ARGS>
+                   : ept == 8  ? k_quantize_buckets<BITS, 8, ARGS>
+                   : ept == 16 ? k_quantize_buckets<BITS, 16, ARGS>
+                               : k_quantize_buckets<BITS, 32, ARGS>;
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, s, tab, tb, scales, B, k0, k1);
 }
 
 }  // namespace
@@ -469,8 +482,20 @@ hipError_t quant_buckets_run(int P, const float* const* vals, const uint64_t* n,
         soff += (n[r] + bucket - 1) / bucket;
         max_n = std::max(max_n, n[r]);
     }
+    // the descriptor table: in the launch's arguments when it fits there (up to
+    // 76 streams), else uploaded first, a launch of 3.2 us beside the one that
+    // codes (a stream of 2^20 in buckets of 1024: 17.1 -> 13.9 us a call; of
+    // 2^24: 29.3 -> 26.4)
     QBDesc* tab = static_cast<QBDesc*>(ws);
-    hipError_t e = upload(tab, host, sizeof(QBDesc) * P, s);
+    Blob tb;
+    tb.nwords = 0;
+    hipError_t e = hipSuccess;
+    if (kQBWords * (uint32_t)P <= (uint32_t)kBlobWords) {
+        tb.nwords = kQBWords * (uint32_t)P;
+        memcpy(tb.words, host, sizeof(QBDesc) * P);
+    } else {
+        e = upload(tab, host, sizeof(QBDesc) * P, s);
+    }
     delete[] host;
     if (e != hipSuccess || max_n == 0) return e;
     const int ept = bucket <= 1024u ? 4 : (int)(bucket / 256u);
@@ -478,9 +503,14 @@ hipError_t quant_buckets_run(int P, const float* const* vals, const uint64_t* n,
     const dim3 grid((uint32_t)((max_n + per_block - 1) / per_block), P);
     const uint32_t k0 = (uint32_t)(seed & 0xFFFFFFFFu), k1 = (uint32_t)(seed >> 32);
     timer_begin(kTQuantCodes, s);
-    if (bits == 2) launch_buckets<2>(grid, ept, s, tab, out_scale, bucket, k0, k1);
-    else if (bits == 4) launch_buckets<4>(grid, ept, s, tab, out_scale, bucket, k0, k1);
-    else launch_buckets<8>(grid, ept, s, tab, out_scale, bucket, k0, k1);
+    auto run = [&](auto args) {
+        constexpr bool A = decltype(args)::value;
+        if (bits == 2) launch_buckets<2, A>(grid, ept, s, tab, tb, out_scale, bucket, k0, k1);
+        else if (bits == 4) launch_buckets<4, A>(grid, ept, s, tab, tb, out_scale, bucket, k0, k1);
+        else launch_buckets<8, A>(grid, ept, s, tab, tb, out_scale, bucket, k0, k1);
+    };
+    if (tb.nwords) run(std::true_type{});
+    else run(std::false_type{});
     timer_end(kTQuantCodes, s);
     return hipGetLastError();
 }
