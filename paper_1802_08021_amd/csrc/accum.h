@@ -34,6 +34,16 @@
 // the pass); 24 ragged ranks, sparse root of 5e7: 333 -> 104 us; 128 ranks
 // that share one support: 3.9 ms -> 0.17 ms.
 //
+// Clusters: where more of a stream than its window ends in a tile, the wave
+// reads on, up to eight windows in flight, and what needs the entries a second
+// time (node sizes, heavy indices) reads those again; heavy indices beyond the
+// rows that fit are taken in rounds of consecutive indices, each of which reads
+// only its own part.  Runs of 4096 indices that all ranks share, 2^17 entries a
+// rank of 2^23: 64 ranks 0.48 ms, 128 ranks 0.95 ms, 256 ranks 2.0 ms (one
+// window at a time, all of them again each round: 1.7, 2.9 and 10.3 ms; the
+// walk named above: 0.85, 1.7 and 3.6 ms).  An even call pays about 1% for the
+// larger code.
+//
 // Node sizes (INFO): the field is then the mask of all P slots present.  With
 // pred the next lower slot present at an entry's index, the two meet in one
 // tree node, and |node| = |left| + |right| - the pairs that meet there: one LDS
@@ -362,17 +372,18 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
         v = 0u;
         if (VALS) v = *reinterpret_cast<g_u32*>(lane_u64(va, s) + ov);
     };
-    // Slot s's window from position w on, as aimed, wherever it ends.
+    // Slot s's window from position w on, wherever it ends.
     auto load_careful = [&](uint32_t s, uint32_t w, uint32_t& x, uint32_t& v) {
         const uint32_t n = lane_u32(end, s), at = min(w, n - 1u), e = last(n, w);
-        x = *reinterpret_cast<g_u32*>(lane_u64(ia, s) + 4u * (e - at));
+        x = *reinterpret_cast<g_u32*>(lane_u64(ib, s) + 4ull * at + 4u * (e - at));
         v = 0u;
-        if (VALS && !QUANT) v = *reinterpret_cast<g_u32*>(lane_u64(va, s) + 4u * (e - at));
+        if (VALS && !QUANT) v = *reinterpret_cast<g_u32*>(lane_u64(vb, s) + 4ull * at + 4u * (e - at));
         if (VALS && QUANT)
-            v = *reinterpret_cast<g_u32*>(lane_u64(va, s) - 4u + ((e >> wlog << 2) - (at >> wlog << 2) + 4u - back(n, e)));
+            v = *reinterpret_cast<g_u32*>(lane_u64(vb, s) + 4ull * (at >> wlog) - 4u +
+                                          ((e >> wlog << 2) - (at >> wlog << 2) + 4u - back(n, e)));
     };
     auto request_all = [&](uint32_t w, uint32_t* x, uint32_t* v, auto careful) {
-        aim(w);
+        if (!decltype(careful)::value) aim(w);
 #pragma unroll
         for (int s = 0; s < SL; ++s) {
             if (decltype(careful)::value) {
@@ -391,7 +402,6 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
         j = x - tlo;
         if (decltype(careful)::value) {
             const uint32_t n = lane_u32(end, s);
-            w = lane_u32(w, s);
             j = lane < n - w ? j : kNone;
             if (QUANT) {
                 const uint32_t e = last(n, w);
@@ -509,7 +519,8 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
             auto slots = [&](auto careful) {
 #pragma unroll
                 for (int q = 0; q < G; ++q) {
-                    view(g + q, win0, x[g + q], v[g + q], tlo, jv[q], vv[q], careful);
+                    view(g + q, decltype(careful)::value ? lane_u32(win0, g + q) : 0u, x[g + q], v[g + q], tlo, jv[q], vv[q],
+                         careful);
                     // (decoded here: moved behind the next requests, it would wait for them)
                     if (VALS) asm volatile("" : "+v"(vv[q]));
                     if (decltype(careful)::value) __builtin_amdgcn_sched_barrier(0);
@@ -530,34 +541,78 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
 #pragma unroll
             for (int q = 0; q < G; ++q) arrive(jv[q], vv[q], old[q], IN[q]);
         }
-        // Windows of slot s from its o-th of this tile on, from memory, while
-        // they hold entries of it: f(index in tile, value, lanes with one).
-        // Returns the entries found.
-        auto walk = [&](uint32_t s, uint32_t o, auto&& f) -> uint32_t {
-            uint32_t n = 0u, got;
-            do {
-                const uint32_t w = min(win0 + 64u * o++, end);
-                aim(w);
-                uint32_t x2, v2, j;
+        // More windows of the slots in `mask`, from memory: from a slot's window
+        // cur (its lane's; 0: the one at win0) on while they end in this tile, at
+        // index jmax at most; cur moves past those.  f(slot, index in tile, value,
+        // lanes with an entry of the tile).  `few` (a tile with a window or two more
+        // than most): first one window a slot, in turn; then kBatch in flight, of
+        // one slot or of as many as are left.
+        constexpr uint32_t kLogBatch = IT > 1u ? 2u : 3u, kBatch = 1u << kLogBatch;
+        auto walk = [&](uint32_t mask, uint32_t& cur, uint32_t jmax, auto few, auto&& f) {
+            auto one = [&](uint32_t s, uint32_t w, uint32_t wx, uint32_t wval) -> bool {
+                uint32_t j;
                 float val;
-                load_careful(s, lane_u32(w, s), x2, v2);
-                view(s, w, x2, v2, tlo, j, val, std::true_type{});
+                view(s, w, wx, wval, tlo, j, val, std::true_type{});
                 const uint64_t in = lanes_lt(j, TT);
-                got = (uint32_t)__popcll(in);
-                n += got;
-                f(j, val, in);
-                if (!(in >> 63)) break;
-            } while (got);
-            return n;
-        };
-        if (full) {  // rare by the choice of T: the windows are continued
-            uint32_t more = 0u;  // entries found, by slot
-            for (uint32_t m = full; m; m &= m - 1u) {
-                const uint32_t s = (uint32_t)__builtin_ctz(m);
-                const uint32_t n =
-                    walk(s, 1u, [&](uint32_t j, float val, uint64_t in) { arrive(j, val, claim(s, j, in), in); });
-                more = lane == s ? n : more;
+                if (in) f(s, j, val, in);
+                const bool past = (in >> 63) != 0u && lane_u32(j, 63u) <= jmax;
+                if (past) cur += lane == s ? 1u : 0u;
+                return past;
+            };
+            auto window = [&](uint32_t s, uint32_t o) -> uint32_t {
+                const uint32_t w0 = lane_u32(win0, s);
+                return w0 + min(64u * o, lane_u32(end, s) - w0);
+            };
+            uint32_t live = decltype(few)::value ? 0u : mask;
+            for (uint32_t m = decltype(few)::value ? mask : 0u; m; m &= m - 1u) {
+                const uint32_t s = (uint32_t)__builtin_ctz(m), w = window(s, lane_u32(cur, s));
+                uint32_t wx, wval;
+                load_careful(s, w, wx, wval);
+                if (one(s, w, wx, wval)) live |= 1u << s;
             }
+            while (__builtin_expect(live != 0u, 0)) {
+                const uint32_t m = (uint32_t)__popc(live);
+                const uint32_t pl = m == 1u ? kLogBatch : (m == 2u ? kLogBatch - 1u : (m <= 4u ? kLogBatch - 2u : 0u));
+                const uint32_t per = (1u << pl) - 1u;
+                // lane u: unit u's slot and window (lane 31 is no slot's: empty)
+                uint32_t us = 31u, uw = kVoid, nu = 0u;
+#pragma unroll 1
+                for (uint32_t rest = live; rest && nu < kBatch; rest &= rest - 1u) {
+                    const uint32_t s = (uint32_t)__builtin_ctz(rest), w0 = lane_u32(win0, s);
+                    const uint32_t o = 64u * (lane_u32(cur, s) + (lane & per));
+                    const bool mine = lane - nu <= per;
+                    us = mine ? s : us;
+                    uw = mine ? w0 + min(o, lane_u32(end, s) - w0) : uw;
+                    nu += per + 1u;
+                }
+                uint32_t x2[kBatch], v2[kBatch];
+#pragma unroll
+                for (uint32_t u = 0; u < kBatch; ++u) {
+                    load_careful(lane_u32(us, u), lane_u32(uw, u), x2[u], v2[u]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                nu = __builtin_amdgcn_readfirstlane((int)min(nu, kBatch));
+                uint32_t going = __builtin_amdgcn_readfirstlane((int)live);
+                asm volatile("" : "+s"(nu), "+s"(going));
+#pragma unroll 1
+                for (uint32_t u = 0; u < nu; ++u) {  // (one copy of the code: the registers move down)
+                    const uint32_t s = lane_u32(us, u);
+                    if ((going >> s & 1u) && !one(s, lane_u32(uw, u), x2[0], v2[0])) going &= ~(1u << s);
+#pragma unroll
+                    for (uint32_t i = 0; i + 1u < kBatch; ++i) {
+                        x2[i] = x2[i + 1u];
+                        v2[i] = v2[i + 1u];
+                    }
+                }
+                live = going;
+            }
+        };
+        if (__builtin_expect(full != 0u, 0)) {  // the windows are continued
+            uint32_t more = 0u, cur = 1u;  // entries found, by slot
+            walk(full, cur, kNone, std::true_type{}, [&](uint32_t s, uint32_t j, float val, uint64_t in) {
+                more += lane == s ? (uint32_t)__popcll(in) : 0u;
+                arrive(j, val, claim(s, j, in), in);
+            });
             cnt += more;
             pos = min(pos + more, upto);
             // (every slot, in the order above: a wait for one of them then
@@ -591,27 +646,28 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
         if (MODE == kAccDense && tile != 0u) store(tile - 1u);
         __syncthreads();
 
-        // The wave's entries in this tile once more: f(slot, index in tile, value).
-        auto again = [&](auto&& f) {
-            uint32_t left = (1u << SL) - 1u;
+        // The wave's entries in this tile once more, at index jmax at most (of
+        // those read again, from window cur on): f(slot, index in tile, value).
+        constexpr uint32_t kCur = KEEP ? 1u : 0u;
+        const uint32_t reread =
+            KEEP ? full : (uint32_t)__builtin_amdgcn_uicmp(cnt, 0u, 33) & ((1u << SL) - 1u);
+        auto again = [&](uint32_t& cur, uint32_t jmax, auto few, auto&& f) {
+            uint32_t in = __builtin_amdgcn_readfirstlane((int)TT);
+            asm volatile("" : "+s"(in));  // (compared anew: eight masks kept over the rounds would not fit the registers)
             if (KEEP) {
 #pragma unroll
                 for (int s = 0; s < G; ++s)
-                    if (jv[s] < TT) f((uint32_t)s, jv[s], vv[s]);
-                left = full;
+                    if (jv[s] < in) f((uint32_t)s, jv[s], vv[s]);
             }
-            for (; left; left &= left - 1u) {
-                const uint32_t s = (uint32_t)__builtin_ctz(left);
-                if (lane_u32(cnt, s))
-                    walk(s, KEEP ? 1u : 0u, [&](uint32_t j, float val, uint64_t) {
-                        if (j < TT) f(s, j, val);
-                    });
-            }
+            walk(reread, cur, jmax, few, [&](uint32_t s, uint32_t j, float val, uint64_t) {
+                if (j < in) f(s, j, val);
+            });
         };
         if (INFO) {
             // each entry and the next lower slot present at its index meet in a
             // node of level h + 1, h their highest differing bit
-            again([&](uint32_t sl, uint32_t j, float) {
+            uint32_t cur = kCur;
+            again(cur, kNone, std::integral_constant<bool, KEEP>{}, [&](uint32_t sl, uint32_t j, float) {
                 const uint32_t r = r0 + sl;
                 uint32_t pred = kNone;
 #pragma unroll
@@ -746,6 +802,14 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
             // Heavy indices, in the planes' space: the owners number them (s_num,
             // kNoNum for the others); rows of P words are cleared, filled by
             // rank and summed into s_out, from where the owners take the sums.
+            // Where there are more than rows, they are numbered in index order and
+            // taken in rounds: each an interval of the tile, so that of the
+            // entries read again a round takes its own part.
+            auto ownedh = [&](uint32_t it) -> bool {
+                uint32_t t = __builtin_amdgcn_readfirstlane((int)T);
+                if (MODE != kAccWrite) asm volatile("" : "+s"(t));  // (as above)
+                return (MODE != kAccWrite || it * 256u < tw) && own(it) < t;
+            };
             constexpr uint32_t kNoNum = 0xFFFFu;
             float* const s_out = s_p;                                        // [T]
             uint16_t* const s_num = reinterpret_cast<uint16_t*>(s_p + T);    // [T]
@@ -757,35 +821,39 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
             uint32_t hm = 0u;  // this thread's
 #pragma unroll
             for (uint32_t it = 0; it < IT; ++it)
-                if (owned(it)) hm |= ((s_hb[own(it) >> 5] >> (own(it) & 31u)) & 15u) << (4u * it);
+                if (ownedh(it)) hm |= ((s_hb[own(it) >> 5] >> (own(it) & 31u)) & 15u) << (4u * it);
             const uint32_t hn = (uint32_t)__popc(hm), hs = wave_scan(hn);
-            uint32_t id0 = 0u;
-            if (lane == 63u && hs) id0 = atomicAdd(&s_nh[par], hs);
-            id0 = lane_u32(id0, 63u) + hs - hn;
+            uint32_t first = 0u;
+            if (lane == 63u && hs) first = atomicAdd(&s_nh[par], hs);
+            first = lane_u32(first, 63u) + hs - hn;
             __syncthreads();
             const uint32_t nh = s_nh[par];
 #pragma unroll
             for (uint32_t it = 0; it < IT; ++it) {
-                if (!owned(it)) continue;
+                if (!ownedh(it)) continue;
                 *reinterpret_cast<uint2*>(&s_num[own(it)]) = make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);
             }
             for (uint32_t i = tid; i < TMAX / 32u; i += NT) s_hb[i] = 0u;
-            for (uint32_t base = 0; base < nh; base += HR) {
-                const uint32_t nr = min(nh - base, HR);
-                uint32_t id = id0 - base;
-                for (uint32_t m = hm; m; m &= m - 1u, ++id) {
+            auto number = [&](uint32_t m, uint32_t id, uint32_t nr) {
+                for (; m; m &= m - 1u, ++id) {
                     const uint32_t q = (uint32_t)__builtin_ctz(m), j = own(q >> 2) + (q & 3u);
                     s_num[j] = (uint16_t)(id < nr ? id : kNoNum);
                     if (id < nr) s_hj[id] = (uint16_t)j;
                 }
+            };
+            auto clear_rows = [&](uint32_t nr) {
                 for (uint32_t i = tid * 4u; i < nr * RS; i += NT * 4u)
                     *reinterpret_cast<float4*>(&s_row[i]) = make_float4(-0.0f, -0.0f, -0.0f, -0.0f);
                 __syncthreads();
-                again([&](uint32_t sl, uint32_t j, float val) {
+            };
+            auto scatter = [&](uint32_t& cur, uint32_t jmax, auto few) {
+                again(cur, jmax, few, [&](uint32_t sl, uint32_t j, float val) {
                     const uint32_t i = s_num[j];
                     if (i != kNoNum) s_row[i * RS + r0 + sl] = val;
                 });
                 __syncthreads();
+            };
+            auto sum_rows = [&](uint32_t nr) {
                 const uint32_t rpw = 64u / lg, sub = lane / lg, q4 = (lane % lg) * 4u;  // lg: a power of two
                 for (uint32_t i0 = wv * rpw; i0 < nr; i0 += NW * rpw) {
                     const uint32_t i = min(i0 + sub, nr - 1u), j = s_hj[i];
@@ -800,10 +868,41 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
                     if (q4 == 0u && i0 + sub < nr) s_out[j] = t;
                 }
                 __syncthreads();
+            };
+            uint32_t cur = kCur;
+            if (__builtin_expect(nh <= HR, 1)) {
+                number(hm, first, nh);
+                clear_rows(nh);
+                scatter(cur, kNone, std::integral_constant<bool, KEEP>{});
+                sum_rows(nh);
+            } else {
+                static_assert(IT * NW <= 64u, "a lane for each wave's 256 indices");
+                uint32_t* const s_ht = s_l;  // their counts, in index order
+                auto part = [&](uint32_t it) -> uint32_t { return MODE == kAccWrite ? wv * IT + it : it * NW + wv; };
+                uint32_t id0[IT];  // the number of the first of four
+#pragma unroll
+                for (uint32_t it = 0; it < IT; ++it) {
+                    const uint32_t n = (uint32_t)__popc(hm >> (4u * it) & 15u), incl = wave_scan(n);
+                    if (lane == 63u) s_ht[part(it)] = incl;
+                    id0[it] = incl - n;
+                }
+                __syncthreads();
+                const uint32_t ht = lane < IT * NW ? s_ht[lane] : 0u, ps = wave_scan(ht) - ht;
+#pragma unroll
+                for (uint32_t it = 0; it < IT; ++it) id0[it] += lane_u32(ps, part(it));
+#pragma unroll 1
+                for (uint32_t base = 0; base < nh; base += HR) {
+                    const uint32_t nr = min(nh - base, HR);
+#pragma unroll
+                    for (uint32_t it = 0; it < IT; ++it) number(hm & 15u << (4u * it), id0[it] - base, nr);
+                    clear_rows(nr);
+                    scatter(cur, __builtin_amdgcn_readfirstlane((int)s_hj[nr - 1u]), std::false_type{});
+                    sum_rows(nr);
+                }
             }
 #pragma unroll
             for (uint32_t it = 0; it < IT; ++it) {
-                if (!owned(it)) continue;
+                if (!ownedh(it)) continue;
                 const uint32_t b = hm >> (4u * it) & 15u;
                 if (b) {
                     const float4 q = *reinterpret_cast<const float4*>(&s_out[own(it)]);

@@ -1,0 +1,65 @@
+"""What a call costs must follow from the entries it moves, whatever their
+shape: a call on indices of one shape is timed against one on as many entries
+of an even shape, both on this device, in turn.  The bounds lie at about the
+geometric mean of the ratios with and without the code that each case is for
+(both stated there, measured on one MI355X)."""
+import pytest
+
+from gpu_util import say, torch_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _time(*calls):
+    """Least time of a call (us), five rounds of the calls in turn."""
+    torch, _ = torch_dev()
+    best = [float("inf")] * len(calls)
+    for _ in range(6):
+        for i, c in enumerate(calls):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            a.record()
+            for _ in range(3):
+                c()
+            b.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b) * 1e3 / 3)
+    return best
+
+
+def _uniform(N, k, r):
+    torch, dev = torch_dev()
+    g = torch.Generator(device=dev)
+    g.manual_seed(1000 + r)
+    a = torch.unique(torch.randint(N, (k + k // 4 + 64,), generator=g, device=dev))
+    return a[torch.randperm(a.numel(), generator=g, device=dev)[:k]].sort().values
+
+
+def _reduce(N, idx, info=False, delta=0.01):
+    from paper_1802_08021_amd import sparcml as S
+    torch, dev = torch_dev()
+    idx = [a.to(torch.int32) for a in idx]
+    vals = [torch.ones(a.numel(), device=dev) for a in idx]
+    return S.ReduceCall(idx, N, delta, vals=vals, node_info=info).run_async
+
+
+def _comb(N, k, run):
+    """Runs of consecutive indices, evenly spread."""
+    torch, dev = torch_dev()
+    n = k // run
+    return ((torch.arange(n, device=dev) * (N // n))[:, None] + torch.arange(run, device=dev)).reshape(-1)
+
+
+# Runs that all ranks share, the same number of them in every part of the
+# range: the tiles they fill hold 64 windows a stream and nothing but heavy
+# indices.  One window at a time, and all of them again for every round of
+# rows: 27.7, 35 and 15.8 times the uniform call; windows in batches, each
+# round its own part: 7.8, 10.9 and 3.5 times.
+@pytest.mark.parametrize("P,bound", [(64, 15.0), (128, 20.0), (256, 7.5)])
+def test_reduce_shared_runs(P, bound):
+    N, k = 1 << 23, 1 << 17
+    even = _reduce(N, [_uniform(N, k, r) for r in range(P)])
+    runs = _reduce(N, [_comb(N, k, 4096)] * P)
+    t0, t1 = _time(even, runs)
+    say(f"[cost] shared runs P={P}: {t1:.1f} us, uniform {t0:.1f} us")
+    assert t1 < bound * t0
