@@ -80,9 +80,11 @@ struct AccArgs {
     uint64_t* node_nnz;
     uint8_t* node_dense;
     const uint32_t* none;    // [kVoid] words 0xFFFFFFFF
+    const uint32_t* odd;     // [P] whether a stream is far from even over the chunks
     uint64_t N, thr, chunk;  // range, threshold, indices per chunk (a multiple of 64)
     uint32_t P, L, T;        // tree slots, log2 P, tile width (a multiple of 64)
     uint32_t nchunks, qbits, lo, out_cap, nfold, when;
+    uint32_t wshift;         // the chunks' weights (acc_cut) are held shifted down by it, their sum in 31 bits
     uint32_t out_vec;        // out_val is 16-byte aligned
 };
 
@@ -226,6 +228,58 @@ __device__ bool acc_root(const AccArgs& a, uint32_t chunk, uint32_t* before, uin
     return dense;
 }
 
+// Where the streams' entries lie unevenly over the chunks, the workgroups take
+// ranges of equal weight instead (entries count twice, indices once: a tile's
+// cost without entries is about half of what it costs with one an index).  A
+// chunk that weighs more than one range is cut into pieces of equal width.
+// From the offsets at the chunks, in every workgroup and every pass alike; s_w
+// holds 2048 words, s_tot 16.  Returns false where no chunk weighs more than
+// 1.5 of the mean.
+// (128 ranks, 1% of 2^22 in one layer of a twentieth of the range: 2.3 -> 0.31
+// ms; a run that all share: 7.5 -> 0.64 ms.)
+__device__ __forceinline__ bool acc_cut(const uint32_t* off, uint32_t P, uint32_t nchunks, uint64_t N, uint64_t chunk,
+                                     uint32_t wshift, uint32_t* s_w, uint32_t* s_tot, uint64_t* from, uint64_t* to)
+{
+    const uint32_t t = threadIdx.x, n = nchunks;
+    // four threads a chunk, each a quarter of the streams
+    for (uint32_t c0 = 0; c0 < n; c0 += 256u) {
+        const uint32_t c = c0 + (t >> 2);
+        uint64_t e = 0;
+        if (c < n)
+            for (uint32_t r = t & 3u; r < P; r += 4u) {
+                const uint32_t* const o = off + (uint64_t)r * (n + 1u) + c;
+                e += max(o[1], o[0]) - o[0];
+            }
+        e += __shfl_xor(e, 1);
+        e += __shfl_xor(e, 2);
+        if (c < n && (t & 3u) == 0u) s_w[c] = (uint32_t)((2u * e + min(chunk, N - c * chunk)) >> wshift);
+    }
+    __syncthreads();
+    const uint32_t w = t < n ? s_w[t] : 0u, incl = wave_scan(w);  // (n <= 1024: a chunk a thread)
+    __syncthreads();
+    if ((t & 63u) == 63u) s_tot[t >> 6] = incl;
+    __syncthreads();
+    uint32_t before = incl - w, sum = 0u;
+    for (uint32_t v = 0; v < 16u; ++v) {
+        if (v < t >> 6) before += s_tot[v];
+        sum += s_tot[v];
+    }
+    if (!__syncthreads_or(2ull * n * w > 3ull * sum + 2u * n)) return false;
+    const uint64_t len = min(chunk, N - min((uint64_t)t * chunk, N));
+    uint64_t* const s_at = reinterpret_cast<uint64_t*>(s_w);
+    if (t < 2u) s_at[t] = N;  // (the last range's end; streams that do not ascend may give others none)
+    __syncthreads();
+    for (uint32_t i = 0; i < 2u; ++i) {
+        const uint64_t at = (uint64_t)(blockIdx.x + i) * sum / n;
+        if (at >= before && at - before < w) s_at[i] = ((uint64_t)t * chunk + (at - before) * len / w) & ~63ull;
+    }
+    __syncthreads();
+    *from = s_at[0];
+    *to = max(s_at[1], s_at[0]);
+    __syncthreads();
+    return true;
+}
+
 // One entry of a sparse root at position o.  Positions come from the union
 // sizes that the counting pass and this one take alike, so for streams that
 // ascend o < root nnz <= out_cap; streams that do not can make them disagree,
@@ -311,6 +365,9 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
     uint64_t ib = reinterpret_cast<uint64_t>(a.none), vb = ib;     // index and value (or code) arrays
     uint32_t end = kVoid, pos = 0u, upto = 0u;  // entries; next one, and past the last of this chunk
     float unitv = 0.0f;
+    uint32_t odd = 0u;
+    for (uint32_t r = lane; r < P; r += 64u) odd |= a.odd[r];
+    uint64_t clo = (uint64_t)chunk * a.chunk, chi = min(clo + a.chunk, a.N);  // this workgroup's indices
     if (lane < (uint32_t)SL && r0 + lane < P) {
         const StreamDesc& d = a.tab[r0 + lane];
         if (d.nnz) {
@@ -327,6 +384,42 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
     auto lane_u64 = [&](uint64_t v, uint32_t l) -> uint64_t {
         return (uint64_t)lane_u32((uint32_t)(v >> 32), l) << 32 | lane_u32((uint32_t)v, l);
     };
+    if (__builtin_expect(lanes_ne(odd, 0u) != 0u, 0) &&
+        acc_cut(a.off, P, a.nchunks, a.N, a.chunk, a.wshift, s_f, s_tot, &clo, &chi)) {
+        clo = lane_u64(clo, 0u);
+        chi = lane_u64(chi, 0u);
+        // The streams' first entries at or past clo, from the chunk it lies in:
+        // 64 places at a time, of all slots together.
+        const uint32_t c0 = (uint32_t)min(clo / a.chunk, (uint64_t)a.nchunks - 1u);
+        const uint32_t c1 = (uint32_t)min((chi + a.chunk - 1u) / a.chunk, (uint64_t)a.nchunks);
+        uint32_t past = pos;
+        if (lane < (uint32_t)SL && r0 + lane < P && ib != reinterpret_cast<uint64_t>(a.none)) {
+            const uint32_t* const o = a.off + (r0 + lane) * (a.nchunks + 1u);
+            pos = min(o[c0], end);
+            past = min(max(o[c0 + 1u], pos), end);
+            upto = min(max(o[c1], pos), end);
+        }
+        const uint32_t first = a.lo + (uint32_t)clo;
+        while (lanes_ne(pos, past)) {
+            uint32_t y[SL];
+#pragma unroll
+            for (int s = 0; s < SL; ++s) {
+                const uint32_t at = lane_u32(pos, s), n = lane_u32(past, s) - at, step = n / 64u + min(n % 64u, 1u);
+                const uint32_t e = at + min(lane * step, n - min(n, 1u));
+                y[s] = *reinterpret_cast<g_u32*>(lane_u64(ib, s) + 4ull * min(e, lane_u32(end, s) - 1u));
+            }
+#pragma unroll
+            for (int s = 0; s < SL; ++s) {
+                const uint32_t at = lane_u32(pos, s), n = lane_u32(past, s) - at, step = n / 64u + min(n % 64u, 1u);
+                const uint32_t below = (uint32_t)__popcll(__ballot(lane * step < n && y[s] < first));
+                // below == 0: the first; else past the last of them and at most at the next
+                const uint32_t a0 = below ? at + (below - 1u) * step + 1u : at, a1 = below ? at + min(below * step, n) : at;
+                pos = lane == (uint32_t)s ? a0 : pos;
+                past = lane == (uint32_t)s ? a1 : past;
+            }
+        }
+        __syncthreads();
+    }
     // Whether a window of this chunk can reach past a stream's end (one starts
     // at `upto` at most): the chunk then takes the careful way through its
     // windows.
@@ -436,9 +529,7 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
         s_heavy[par] = 1u;
     };
 
-    const uint64_t clo = (uint64_t)chunk * a.chunk;
-    const uint32_t cw = (uint32_t)min(a.chunk, a.N - clo);  // this chunk's indices
-    const uint32_t ntiles = (cw + T - 1u) / T;
+    const uint32_t cw = (uint32_t)(chi - clo), ntiles = (uint32_t)(((uint64_t)cw + T - 1u) / T);
     // Output of tile t of the chunk, kept in registers until the next tile's
     // arrivals are done: loads and stores complete in order, so a store shortly
     // before a wait for windows would be waited for as well.
@@ -573,7 +664,7 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
             while (__builtin_expect(live != 0u, 0)) {
                 const uint32_t m = (uint32_t)__popc(live);
                 const uint32_t pl = m == 1u ? kLogBatch : (m == 2u ? kLogBatch - 1u : (m <= 4u ? kLogBatch - 2u : 0u));
-                const uint32_t per = (1u << pl) - 1u;
+                const uint32_t per = (1u << (jmax == kNone ? pl : min(pl, 1u))) - 1u;  // (a round takes one or two)
                 // lane u: unit u's slot and window (lane 31 is no slot's: empty)
                 uint32_t us = 31u, uw = kVoid, nu = 0u;
 #pragma unroll 1
@@ -588,6 +679,7 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
                 uint32_t x2[kBatch], v2[kBatch];
 #pragma unroll
                 for (uint32_t u = 0; u < kBatch; ++u) {
+                    if (u >= nu) break;
                     load_careful(lane_u32(us, u), lane_u32(uw, u), x2[u], v2[u]);
                     __builtin_amdgcn_sched_barrier(0);
                 }

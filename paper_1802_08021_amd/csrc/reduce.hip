@@ -19,7 +19,8 @@
 //    (no two children hold more than 2 U).
 //
 // Passes, none of which waits for the host: partition (per-chunk stream
-// offsets) -> dense pass, when the streams hold more than thr entries together
+// offsets; where a stream lies unevenly over the chunks, the workgroups of the
+// passes below take ranges of equal weight instead) -> dense pass, when the streams hold more than thr entries together
 // (with the node sizes if the caller wants them), else a counting pass ->
 // (without node sizes) a counting pass of the node sizes, which returns at once
 // unless thr/2 < U <= thr -> sparse output, which applies the rule, reports the
@@ -91,9 +92,9 @@ constexpr uint32_t kPartSamples = 1024;
 __global__ void __launch_bounds__(256) k_partition(StreamDesc* tab, DescArgs tb, uint32_t* off, uint32_t nchunks,
                                                    uint64_t chunk_coords, uint64_t lo, uint64_t N, uint32_t* zero,
                                                    uint32_t nzero, ReduceResult* hdr, ReduceResult* res,
-                                                   uint32_t qbits, uint32_t* pad, uint32_t* none)
+                                                   uint32_t qbits, uint32_t* pad, uint32_t* none, uint32_t* odd)
 {
-    __shared__ uint32_t s_smp[kPartSamples];
+    __shared__ uint32_t s_smp[kPartSamples], s_off[kSegMax + 1];
     const uint32_t r = blockIdx.x, tid = threadIdx.x;
     if (r == 0) {
         for (uint32_t i = tid; i < nzero; i += blockDim.x) zero[i] = 0u;
@@ -142,7 +143,16 @@ __global__ void __launch_bounds__(256) k_partition(StreamDesc* tab, DescArgs tb,
             res = lower_bound(idx, min(pa, pb), pb, x);
         }
         o[c] = res;
+        s_off[c] = res;
     }
+    __syncthreads();
+    // Whether a chunk holds far more of the stream than the others (never, of
+    // an evenly drawn one: half of the mean and 64 are six deviations or more)
+    const uint32_t most = nnz / nchunks + nnz / nchunks / 2u + 64u;
+    bool far = false;
+    for (uint32_t c = tid; c < nchunks; c += blockDim.x) far |= s_off[c + 1u] > s_off[c] && s_off[c + 1u] - s_off[c] > most;
+    const int any = __syncthreads_or(far);
+    if (tid == 0) odd[r] = any ? 1u : 0u;
 }
 
 // Per-segment start offsets of every stream by one pass over its entries,
@@ -221,7 +231,7 @@ uint32_t compute_units()
 
 struct Layout {
     StreamDesc* tab;
-    uint32_t *off, *zero, *node_cnt, *chunk_ne, *pad, *none;
+    uint32_t *off, *zero, *node_cnt, *odd, *chunk_ne, *pad, *none;
     ReduceResult* hdr;
     size_t bytes;
 };
@@ -236,7 +246,9 @@ Layout layout(const ReducePlan& p, void* ws)
     l.off = c.take<uint32_t>((size_t)p.P * (kSegMax + 1));
     l.zero = c.take<uint32_t>(std::max<size_t>((size_t)p.P + 1, kSegStateWords + 2 * (size_t)kSegMax));
     l.node_cnt = l.zero;
-    // union sizes of the chunks, behind the node counters (at most 256)
+    // behind the node counters (at most 255) a word a stream, and the union
+    // sizes of the chunks
+    l.odd = l.zero ? l.zero + 256 : nullptr;
     l.chunk_ne = l.zero ? l.zero + 512 : nullptr;
     // and a word per stream for codes of less than one
     l.pad = l.zero ? l.zero + 512 + kSegMax : nullptr;
@@ -349,9 +361,9 @@ hipError_t reduce_run(const ReducePlan& p, const StreamDesc* host_tab, uint32_t*
         hipLaunchKernelGGL(k_partition_pass, dim3((uint32_t)((nthreads + 255) / 256), p.P), dim3(256), 0, s, l.tab,
                            tb, l.off, p.nseg, p.segw, p.lo, l.zero, nzero);
     } else {
-        const uint32_t nzero = p.P + 1u;
+        const uint32_t nzero = p.P;
         hipLaunchKernelGGL(k_partition, dim3(p.P), dim3(256), 0, s, l.tab, tb, l.off, p.nchunks, p.chunk, p.lo,
-                           p.N, l.zero, nzero, l.hdr, dev_result, p.qbits, l.pad, l.none);
+                           p.N, l.zero, nzero, l.hdr, dev_result, p.qbits, l.pad, l.none, l.odd);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
 
@@ -377,6 +389,8 @@ hipError_t reduce_run(const ReducePlan& p, const StreamDesc* host_tab, uint32_t*
     a.chunk_ne = l.chunk_ne;
     a.node_cnt = l.node_cnt;
     a.none = l.none;
+    a.odd = l.odd;
+    for (uint64_t w = 2u * p.sum_nnz + p.N; w >> a.wshift >= 1ull << 31;) ++a.wshift;
     a.out_idx = out_idx;
     a.out_val = out_val;
     a.hdr = l.hdr;

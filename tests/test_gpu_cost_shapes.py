@@ -63,3 +63,26 @@ def test_reduce_shared_runs(P, bound):
     t0, t1 = _time(even, runs)
     say(f"[cost] shared runs P={P}: {t1:.1f} us, uniform {t0:.1f} us")
     assert t1 < bound * t0
+
+
+# Entries that crowd into a part of the range, 128 ranks: with a workgroup for
+# every part of the range alike, a few of them do all the work, 46, 159 and 62
+# times the uniform call; with ranges of equal weight 9.7, 5.3 and 9.2 times.
+@pytest.mark.parametrize("shape,bound", [("layer", 17.0), ("run", 45.0), ("low", 20.0)])
+def test_reduce_crowded(shape, bound):
+    torch, dev = torch_dev()
+    P, N, k = 128, 1 << 22, (1 << 22) // 100
+
+    def crowd(r):
+        if shape == "run":
+            return torch.arange(N // 5, N // 5 + k, device=dev)
+        if shape == "layer":
+            return N // 3 + _uniform(N // 20, k, r)
+        g = torch.Generator(device=dev)
+        g.manual_seed(50 + r)
+        return torch.unique((N * torch.rand(2 * k, generator=g, device=dev, dtype=torch.float64) ** 6).long())[:k]
+
+    even = _reduce(N, [_uniform(N, k, r) for r in range(P)])
+    t0, t1 = _time(even, _reduce(N, [crowd(r) for r in range(P)]))
+    say(f"[cost] crowded {shape}: {t1:.1f} us, uniform {t0:.1f} us")
+    assert t1 < bound * t0
