@@ -415,9 +415,14 @@ hipError_t reduce_run(const ReducePlan& p, const StreamDesc* host_tab, uint32_t*
     // room for three standard deviations of a uniform stream; of streams of
     // many lengths the longest may have 52 (one window in 20 is continued; 48
     // ragged ranks of 2e7 with node sizes: 145 -> 137 us by the wider tiles).
+    // Up to 16 slots a wave has one stream, and 15 waves of 16 may have none: there
+    // a tile takes eight windows of it, the others read on together (2 and 8
+    // ranks, 10% of 2^25, 4-bit codes: 540 -> 156 and 353 -> 175 us; two streams a
+    // wave gain and lose alike, 32 ranks, 10% of 2^22: 91 -> 86, 2^20: 35 -> 40).
     const uint64_t live = std::max<uint64_t>(p.P / 2u + nfold, 1u), mean = (p.sum_nnz + live - 1u) / live;
+    const uint64_t wide = p.P <= 16u ? 8u : 1u;
     auto shape = [&](uint32_t tmax) {
-        const uint64_t fit = p.max_nnz ? std::min(44ull * p.N / mean, 52ull * p.N / p.max_nnz) : tmax;
+        const uint64_t fit = p.max_nnz ? std::min(44u * wide * p.N / mean, 52u * wide * p.N / p.max_nnz) : tmax;
         const uint64_t most = std::min<uint64_t>(tmax, std::max<uint64_t>(fit & ~63ull, 256));
         const uint64_t n = (p.chunk + most - 1) / most;
         a.T = (uint32_t)((((p.chunk + n - 1) / n) + 63) & ~63ull);

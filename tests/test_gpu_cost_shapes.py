@@ -86,3 +86,17 @@ def test_reduce_crowded(shape, bound):
     t0, t1 = _time(even, _reduce(N, [crowd(r) for r in range(P)]))
     say(f"[cost] crowded {shape}: {t1:.1f} us, uniform {t0:.1f} us")
     assert t1 < bound * t0
+
+
+# Few ranks, one entry in ten indices against one in 160: with tiles that hold
+# one window of a stream the denser call takes 6.8, 6.9 and 4.5 times as long
+# (its tiles are narrow, and most waves idle); with eight windows 3.0, 3.3 and
+# 3.2 times.
+@pytest.mark.parametrize("P,bound", [(2, 4.6), (4, 4.8), (8, 3.9)])
+def test_reduce_few_dense_ranks(P, bound):
+    N = 1 << 24
+    thin = _reduce(N, [_uniform(N, N // 160, r) for r in range(P)], delta=1e-3)
+    thick = _reduce(N, [_uniform(N, N // 10, r) for r in range(P)], delta=1e-3)
+    t0, t1 = _time(thin, thick)
+    say(f"[cost] few ranks P={P}: {t1:.1f} us, a sixteenth of the entries {t0:.1f} us")
+    assert t1 < bound * t0
