@@ -429,10 +429,10 @@ GROUP_NAMES = {0: "reduce_tiles", 1: "reduce_write", 2: "reduce_slow", 3: "qsgd_
 # the sources each kernel group is built from (a change of code in them
 # invalidates its measured traffic)
 GROUP_SOURCES = {
-    "reduce_tiles": ("accum.h", "accum_dense.hip", "accum_info.hip", "accum_count.hip", "reduce.hip",
+    "reduce_tiles": ("accum.h", "accum_dense.hip", "accum_info.hip", "accum_count.hip", "accum_pairs.hip", "reduce.hip",
                      "qsgd_device.h", "internal.h"),
     "reduce_write": ("accum.h", "accum_write.hip", "reduce.hip", "qsgd_device.h", "internal.h"),
-    "reduce_slow": ("accum.h", "accum_count.hip", "reduce.hip", "qsgd_device.h", "internal.h"),
+    "reduce_slow": ("accum.h", "accum_count.hip", "accum_pairs.hip", "reduce.hip", "qsgd_device.h", "internal.h"),
     "reduce_merge": ("merge.hip", "qsgd_device.h", "internal.h"),
     "qsgd_norm": ("quant.hip", "internal.h"),
     "qsgd_codes": ("quant.hip", "internal.h"),

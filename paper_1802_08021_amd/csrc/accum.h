@@ -48,6 +48,7 @@
 // pred the next lower slot present at an entry's index, the two meet in one
 // tree node, and |node| = |left| + |right| - the pairs that meet there: one LDS
 // histogram over the nodes is all that is counted.
+// (Where few indices have two entries, accum_pairs.hip counts them instead.)
 #pragma once
 
 #include "internal.h"
@@ -111,6 +112,7 @@ constexpr uint32_t acc_tmax(uint32_t nb, bool info, uint32_t pmax)
 hipError_t acc_dense_launch(const AccArgs& a, uint32_t nb, bool info, hipStream_t s);
 hipError_t acc_count_launch(const AccArgs& a, bool info, hipStream_t s);
 hipError_t acc_write_launch(const AccArgs& a, uint32_t nb, hipStream_t s);
+hipError_t acc_pairs_launch(AccArgs a, uint64_t sum_nnz, hipStream_t s);  // node sizes alone (accum_pairs.hip)
 
 #ifdef __HIPCC__
 namespace {
@@ -280,6 +282,43 @@ __device__ __forceinline__ bool acc_cut(const uint32_t* off, uint32_t P, uint32_
     return true;
 }
 
+__device__ __forceinline__ uint32_t lane_u32(uint32_t v, uint32_t l)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l);
+}
+__device__ __forceinline__ uint64_t lane_u64(uint64_t v, uint32_t l)
+{
+    return (uint64_t)lane_u32((uint32_t)(v >> 32), l) << 32 | lane_u32((uint32_t)v, l);
+}
+
+// The first entries of SL streams (lane s: stream s's indices ib, of `end`)
+// whose index is at least x, each known to lie at pos to past: 64 places at a
+// time, of all streams together.
+template <int SL>
+__device__ __forceinline__ uint32_t find_first(uint64_t ib, uint32_t end, uint32_t pos, uint32_t past, uint32_t x)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    while (lanes_ne(pos, past)) {
+        uint32_t y[SL];
+#pragma unroll
+        for (int s = 0; s < SL; ++s) {
+            const uint32_t at = lane_u32(pos, s), n = lane_u32(past, s) - at, step = n / 64u + min(n % 64u, 1u);
+            const uint32_t e = at + min(lane * step, n - min(n, 1u));
+            y[s] = *reinterpret_cast<g_u32*>(lane_u64(ib, s) + 4ull * min(e, lane_u32(end, s) - 1u));
+        }
+#pragma unroll
+        for (int s = 0; s < SL; ++s) {
+            const uint32_t at = lane_u32(pos, s), n = lane_u32(past, s) - at, step = n / 64u + min(n % 64u, 1u);
+            const uint32_t below = (uint32_t)__popcll(__ballot(lane * step < n && y[s] < x));
+            // none below: the first; else past the last of them and at most at the next
+            const uint32_t a0 = below ? at + (below - 1u) * step + 1u : at, a1 = below ? at + min(below * step, n) : at;
+            pos = lane == (uint32_t)s ? a0 : pos;
+            past = lane == (uint32_t)s ? a1 : past;
+        }
+    }
+    return pos;
+}
+
 // One entry of a sparse root at position o.  Positions come from the union
 // sizes that the counting pass and this one take alike, so for streams that
 // ascend o < root nnz <= out_cap; streams that do not can make them disagree,
@@ -380,16 +419,11 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
         }
         if (QUANT && VALS) unitv = level_unit(*d.qscale, a.qbits);
     }
-    auto lane_u32 = [](uint32_t v, uint32_t l) -> uint32_t { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l); };
-    auto lane_u64 = [&](uint64_t v, uint32_t l) -> uint64_t {
-        return (uint64_t)lane_u32((uint32_t)(v >> 32), l) << 32 | lane_u32((uint32_t)v, l);
-    };
     if (__builtin_expect(lanes_ne(odd, 0u) != 0u, 0) &&
         acc_cut(a.off, P, a.nchunks, a.N, a.chunk, a.wshift, s_f, s_tot, &clo, &chi)) {
         clo = lane_u64(clo, 0u);
         chi = lane_u64(chi, 0u);
-        // The streams' first entries at or past clo, from the chunk it lies in:
-        // 64 places at a time, of all slots together.
+        // The streams' first entries at or past clo, from the chunk it lies in.
         const uint32_t c0 = (uint32_t)min(clo / a.chunk, (uint64_t)a.nchunks - 1u);
         const uint32_t c1 = (uint32_t)min((chi + a.chunk - 1u) / a.chunk, (uint64_t)a.nchunks);
         uint32_t past = pos;
@@ -400,24 +434,7 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
             upto = min(max(o[c1], pos), end);
         }
         const uint32_t first = a.lo + (uint32_t)clo;
-        while (lanes_ne(pos, past)) {
-            uint32_t y[SL];
-#pragma unroll
-            for (int s = 0; s < SL; ++s) {
-                const uint32_t at = lane_u32(pos, s), n = lane_u32(past, s) - at, step = n / 64u + min(n % 64u, 1u);
-                const uint32_t e = at + min(lane * step, n - min(n, 1u));
-                y[s] = *reinterpret_cast<g_u32*>(lane_u64(ib, s) + 4ull * min(e, lane_u32(end, s) - 1u));
-            }
-#pragma unroll
-            for (int s = 0; s < SL; ++s) {
-                const uint32_t at = lane_u32(pos, s), n = lane_u32(past, s) - at, step = n / 64u + min(n % 64u, 1u);
-                const uint32_t below = (uint32_t)__popcll(__ballot(lane * step < n && y[s] < first));
-                // below == 0: the first; else past the last of them and at most at the next
-                const uint32_t a0 = below ? at + (below - 1u) * step + 1u : at, a1 = below ? at + min(below * step, n) : at;
-                pos = lane == (uint32_t)s ? a0 : pos;
-                past = lane == (uint32_t)s ? a1 : past;
-            }
-        }
+        pos = find_first<SL>(ib, end, pos, past, first);
         __syncthreads();
     }
     // Whether a window of this chunk can reach past a stream's end (one starts
@@ -594,11 +611,14 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
             }
         };
         // The windows' in-tile entries (a prefix, streams ascend).  Up to 8
-        // slots a wave keep theirs for the rest of the tile.
+        // slots a wave keep theirs for the rest of the tile; 16 slots keep only the
+        // indices, two a register (0xFFFF: none), or nothing.
         constexpr int G = SL < 8 ? SL : 8;
         constexpr bool KEEP = SL <= 8;
         uint32_t jv[G];
         float vv[G];
+        constexpr bool PACK = !KEEP && NB == 8;  // (at two blocks the tile is wide, and its outputs take the registers)
+        uint32_t jp[PACK ? SL / 2 : 1];
         const uint32_t win0 = pos & ~wmask;
         uint32_t cnt = 0u, full = 0u;  // entries by slot; slots whose window's last entry lies in the tile
         uint32_t near = edge;
@@ -616,6 +636,10 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
                     if (VALS) asm volatile("" : "+v"(vv[q]));
                     if (decltype(careful)::value) __builtin_amdgcn_sched_barrier(0);
                     IN[q] = lanes_lt(jv[q], TT);
+                    if (PACK) {
+                        const uint32_t jj = in_mask(IN[q]) ? jv[q] : 0xFFFFu, h = PACK ? (g + q) / 2 : 0u;
+                        jp[h] = q & 1 ? jp[h] | jj << 16 : jj;
+                    }
                     asm("v_writelane_b32 %0, %1, %2"
                         : "+v"(cnt) : "s"(__builtin_amdgcn_readfirstlane((int)__popcll(IN[q]))), "n"(g + q));
                 }
@@ -638,7 +662,7 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
         // lanes with an entry of the tile).  `few` (a tile with a window or two more
         // than most): first one window a slot, in turn; then kBatch in flight, of
         // one slot or of as many as are left.
-        constexpr uint32_t kLogBatch = IT > 1u ? 2u : 3u, kBatch = 1u << kLogBatch;
+        constexpr uint32_t kLogBatch = IT > 1u || !KEEP ? 2u : 3u, kBatch = 1u << kLogBatch;
         auto walk = [&](uint32_t mask, uint32_t& cur, uint32_t jmax, auto few, auto&& f) {
             auto one = [&](uint32_t s, uint32_t w, uint32_t wx, uint32_t wval) -> bool {
                 uint32_t j;
@@ -740,26 +764,37 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
 
         // The wave's entries in this tile once more, at index jmax at most (of
         // those read again, from window cur on): f(slot, index in tile, value).
+        // Without the values kept, the windows are read again of the slots that
+        // have an entry where(index) wants it; without the indices, of all.
         constexpr uint32_t kCur = KEEP ? 1u : 0u;
-        const uint32_t reread =
-            KEEP ? full : (uint32_t)__builtin_amdgcn_uicmp(cnt, 0u, 33) & ((1u << SL) - 1u);
-        auto again = [&](uint32_t& cur, uint32_t jmax, auto few, auto&& f) {
-            uint32_t in = __builtin_amdgcn_readfirstlane((int)TT);
+        auto kept = [&](int s) -> uint32_t { return KEEP ? jv[KEEP ? s : 0] : jp[PACK ? s / 2 : 0] >> (16 * (s & 1)) & 0xFFFFu; };
+        auto again = [&](uint32_t& cur, uint32_t jmax, auto few, auto&& where, auto&& f) {
+            uint32_t in = __builtin_amdgcn_readfirstlane((int)TT), reread = full;
             asm volatile("" : "+s"(in));  // (compared anew: eight masks kept over the rounds would not fit the registers)
             if (KEEP) {
 #pragma unroll
                 for (int s = 0; s < G; ++s)
                     if (jv[s] < in) f((uint32_t)s, jv[s], vv[s]);
+            } else if (!PACK) {
+                reread = (uint32_t)__builtin_amdgcn_uicmp(cnt, 0u, 33) & ((1u << SL) - 1u);
+            } else {
+#pragma unroll
+                for (int s = 0; s < SL; ++s) {
+                    const uint32_t j = kept(s);
+                    bool hit = false;
+                    if (j < in) hit = where(j);
+                    if (__ballot(hit)) reread |= 1u << s;
+                }
             }
             walk(reread, cur, jmax, few, [&](uint32_t s, uint32_t j, float val, uint64_t) {
                 if (j < in) f(s, j, val);
             });
         };
         if (INFO) {
+            static_assert(!INFO || KEEP || PACK, "indices kept");
             // each entry and the next lower slot present at its index meet in a
             // node of level h + 1, h their highest differing bit
-            uint32_t cur = kCur;
-            again(cur, kNone, std::integral_constant<bool, KEEP>{}, [&](uint32_t sl, uint32_t j, float) {
+            auto meet = [&](uint32_t sl, uint32_t j) {
                 const uint32_t r = r0 + sl;
                 uint32_t pred = kNone;
 #pragma unroll
@@ -772,6 +807,13 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
                     const uint32_t h = 31u - (uint32_t)__clz(pred ^ r);
                     atomicAdd(&s_E[P - (P >> h) + (r >> (h + 1u))], 1u);
                 }
+            };
+#pragma unroll
+            for (int s = 0; s < SL; ++s)
+                if (kept(s) < TT) meet((uint32_t)s, kept(s));
+            uint32_t cur = 1u;
+            walk(full, cur, kNone, std::true_type{}, [&](uint32_t s, uint32_t j, float, uint64_t) {
+                if (j < TT) meet(s, j);
             });
         }
         if (VALS) {
@@ -939,7 +981,7 @@ __global__ void __launch_bounds__(1024, 4) k_acc(AccArgs a)
                 __syncthreads();
             };
             auto scatter = [&](uint32_t& cur, uint32_t jmax, auto few) {
-                again(cur, jmax, few, [&](uint32_t sl, uint32_t j, float val) {
+                again(cur, jmax, few, [&](uint32_t j) { return s_num[j] != kNoNum; }, [&](uint32_t sl, uint32_t j, float val) {
                     const uint32_t i = s_num[j];
                     if (i != kNoNum) s_row[i * RS + r0 + sl] = val;
                 });

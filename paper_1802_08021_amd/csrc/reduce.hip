@@ -20,12 +20,14 @@
 //
 // Passes, none of which waits for the host: partition (per-chunk stream
 // offsets; where a stream lies unevenly over the chunks, the workgroups of the
-// passes below take ranges of equal weight instead) -> dense pass, when the streams hold more than thr entries together
-// (with the node sizes if the caller wants them), else a counting pass ->
-// (without node sizes) a counting pass of the node sizes, which returns at once
-// unless thr/2 < U <= thr -> sparse output, which applies the rule, reports the
-// header and the nodes, and returns at once if the root is dense.  All-sparse
-// inputs of up to 64 slots and 2^21 entries go to the merge tree (merge.hip).
+// passes below take ranges of equal weight instead) -> dense pass, when the
+// streams hold more than thr entries together (with the node sizes if the
+// caller wants them and the streams meet often), else a counting pass -> a pass
+// for the node sizes, from the indices alone or in tiles: where the caller
+// wants them, or, after a dense pass, returning at once unless thr/2 < U <= thr
+// -> sparse output, which applies the rule, reports the header and the nodes,
+// and returns at once if the root is dense.  All-sparse inputs of up to 64
+// slots and 2^21 entries go to the merge tree (merge.hip).
 #include "internal.h"
 
 #include "accum.h"
@@ -409,7 +411,7 @@ hipError_t reduce_run(const ReducePlan& p, const StreamDesc* host_tab, uint32_t*
     a.nfold = nfold;
     a.out_vec = (reinterpret_cast<uintptr_t>(out_val) & 15u) == 0 ? 1u : 0u;
     const bool info = node_nnz || node_dense;
-    const uint32_t nb = acc_blocks(p.sum_nnz, p.N), pmax = std::max<uint32_t>(p.P, 16u);
+    const uint32_t pmax = std::max<uint32_t>(p.P, 16u), nb = acc_blocks(p.sum_nnz, p.N);
     // Tiles of equal width in every chunk, at most tmax wide and narrow enough
     // that a stream's entries usually fit one window of 64: a mean of 44 leaves
     // room for three standard deviations of a uniform stream; of streams of
@@ -430,18 +432,27 @@ hipError_t reduce_run(const ReducePlan& p, const StreamDesc* host_tab, uint32_t*
         // multiples, or the last few would cost as much)
         if (a.T > 4096u) a.T = std::min<uint32_t>((a.T + 4095u) & ~4095u, (uint32_t)most & ~4095u);
     };
+    // Node sizes from the indices alone (a launch more, where a dense pass goes
+    // before it), or in the tile pass: by the mean entries an index.  Dense root,
+    // 2^25, us without and with: 2 ranks 0.25 294, 194; 16 ranks 0.5 340, 285 and
+    // 2 688, 513; 32 ranks 0.1 77, 64 and 0.25 99, 152; 64 ranks 0.25 138, 115 and
+    // 0.5 167, 191; 128 ranks 0.25 246, 129, 0.5 292, 250 and 1 335, 414; 256
+    // ranks 0.1 1168, 232 and 1 2332, 967.  Below 2^22 indices the launch shows
+    // (2^20, 64 ranks, 0.25: 22, 30).
+    const uint64_t most = pmax <= 16u ? 16u : (pmax <= 32u ? 1u : (pmax <= 64u ? 2u : (pmax <= 128u ? 4u : 16u)));  // eighths
+    const bool pairs = (p.N >= 1u << 22 || pmax > 128u) && 8u * p.sum_nnz <= most * p.N;
+    a.when = info ? kWhenNodes : (p.speculate_dense ? kWhenUnion : kWhenSparse);
     if (p.speculate_dense) {
-        a.when = info ? kWhenNodes : kWhenUnion;
-        shape(acc_tmax(nb, info, pmax));
-        if ((e = acc_dense_launch(a, nb, info, s)) != hipSuccess) return e;
-        if (!info) {
-            shape(acc_tmax(nb, true, pmax));
-            if ((e = acc_count_launch(a, true, s)) != hipSuccess) return e;
-        }
-    } else {
-        a.when = info ? kWhenNodes : kWhenSparse;
-        shape(acc_tmax(2u, info, pmax));
-        if ((e = acc_count_launch(a, info, s)) != hipSuccess) return e;
+        const bool with = info && !pairs;
+        shape(acc_tmax(nb, with, pmax));
+        if ((e = acc_dense_launch(a, nb, with, s)) != hipSuccess) return e;
+    }
+    if (a.when != kWhenSparse && pairs) {
+        if ((e = acc_pairs_launch(a, p.sum_nnz, s)) != hipSuccess) return e;
+    } else if (!p.speculate_dense || !info) {
+        const bool nodes = a.when != kWhenSparse;
+        shape(acc_tmax(nodes ? nb : 2u, nodes, pmax));
+        if ((e = acc_count_launch(a, nodes, s)) != hipSuccess) return e;
     }
     shape(acc_tmax(nb, false, pmax));
     if ((e = acc_write_launch(a, nb, s)) != hipSuccess) return e;

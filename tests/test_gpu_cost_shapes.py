@@ -100,3 +100,16 @@ def test_reduce_few_dense_ranks(P, bound):
     t0, t1 = _time(thin, thick)
     say(f"[cost] few ranks P={P}: {t1:.1f} us, a sixteenth of the entries {t0:.1f} us")
     assert t1 < bound * t0
+
+
+# Node sizes where few indices have two entries, against the call without
+# them.  In the tile pass, whose tiles are narrow there, 5.1, 2.3 and 1.9 times
+# as long; from the indices alone 1.2, 1.3 and 1.4 times.
+@pytest.mark.parametrize("P,k,bound", [(256, 1 << 14, 2.5), (128, 1 << 14, 1.7), (64, 1 << 15, 1.65)])
+def test_reduce_node_sizes(P, k, bound):
+    N = 1 << 24
+    idx = [_uniform(N, k, r) for r in range(P)]
+    t0, t1 = _time(_reduce(N, idx), _reduce(N, idx, info=True))
+    say(f"[cost] node sizes P={P}: {t1:.1f} us, without {t0:.1f} us")
+    assert t1 < bound * t0
+
