@@ -92,12 +92,23 @@ struct AccArgs {
 // Blocks of a pass with values, by the mean entries per index (of all
 // streams together): the fewer, the fewer planes to read and the wider the
 // tile; the more, the fewer third arrivals.  Two up to a mean of 0.4 (one
-// heavy index in 450), four up to 1.6 (one in 30 at 1.28), else eight.  With
-// node sizes: eight where a quarter of the slots would not fit a mask word.
-inline uint32_t acc_blocks(uint64_t sum_nnz, uint64_t N)
+// heavy index in 450), four up to 1.6 (one in 30 at 1.28), else eight.  But
+// (2^25 indices, fp32, us):
+// - 8 slots: four blocks hold two ranks each, and no index is ever heavy; two up
+//   to 0.25 (0.35: 197, with four 115);
+// - 16 slots: the wide tile pays up to 1.5 (0.5: 244 with four, 145 with two;
+//   0.7 291, 240; 1 313, 288; 1.4 361, 347);
+// - above 128 slots a tile's heavy indices cost a second look at 16 slots a
+//   wave: two up to 0.5, then eight at once (256 slots, 0.5: 507 with four, 365
+//   with two; 0.75 564 with four, 412 with eight; 1 614, 450; 1.4 1086, 544).
+inline uint32_t acc_blocks(uint64_t sum_nnz, uint64_t N, uint32_t P)
 {
+    if (P > 128u) return 2u * sum_nnz <= N ? 2u : 8u;
+    if (P == 8u && 4u * sum_nnz > N && 5u * sum_nnz <= 8u * N) return 4u;
+    if (P == 16u && 2u * sum_nnz <= 3u * N) return 2u;
     return 5u * sum_nnz <= 2u * N ? 2u : (5u * sum_nnz <= 8u * N ? 4u : 8u);
 }
+// With node sizes: eight where a quarter of the slots would not fit a mask word.
 constexpr uint32_t acc_info_blocks(uint32_t pmax) { return pmax <= 128u ? 4u : 8u; }
 
 // Widest tile: NB planes of T values in 128 KB of LDS, and at four blocks
@@ -1115,7 +1126,7 @@ hipError_t acc_launch_p(const AccArgs& a, hipStream_t s)
     if (a.P <= 32u) return acc_launch<2, INFO ? acc_info_blocks(32) : NB, MODE, INFO, QUANT>(a, s);
     if (a.P <= 64u) return acc_launch<4, INFO ? acc_info_blocks(64) : NB, MODE, INFO, QUANT>(a, s);
     if (a.P <= 128u) return acc_launch<8, INFO ? acc_info_blocks(128) : NB, MODE, INFO, QUANT>(a, s);
-    return acc_launch<16, INFO ? acc_info_blocks(256) : NB, MODE, INFO, QUANT>(a, s);
+    return acc_launch<16, INFO ? acc_info_blocks(256) : (NB == 4 ? 8 : NB), MODE, INFO, QUANT>(a, s);
 }
 
 }  // namespace

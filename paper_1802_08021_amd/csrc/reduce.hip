@@ -411,7 +411,7 @@ hipError_t reduce_run(const ReducePlan& p, const StreamDesc* host_tab, uint32_t*
     a.nfold = nfold;
     a.out_vec = (reinterpret_cast<uintptr_t>(out_val) & 15u) == 0 ? 1u : 0u;
     const bool info = node_nnz || node_dense;
-    const uint32_t pmax = std::max<uint32_t>(p.P, 16u), nb = acc_blocks(p.sum_nnz, p.N);
+    const uint32_t pmax = std::max<uint32_t>(p.P, 16u), nb = acc_blocks(p.sum_nnz, p.N, p.P);
     // Tiles of equal width in every chunk, at most tmax wide and narrow enough
     // that a stream's entries usually fit one window of 64: a mean of 44 leaves
     // room for three standard deviations of a uniform stream; of streams of

@@ -113,3 +113,14 @@ def test_reduce_node_sizes(P, k, bound):
     say(f"[cost] node sizes P={P}: {t1:.1f} us, without {t0:.1f} us")
     assert t1 < bound * t0
 
+
+# Just more entries an index, where the tile pass cuts the ranks into more
+# blocks: its tiles narrow to a quarter.  With the same rule for every number of
+# ranks 1.3 to 1.5 times the entries cost 1.6, 2.3 and 2.1 times the time; with
+# its own above 128 ranks and at 8 and 16 1.3, 1.3 and 1.1 times.
+@pytest.mark.parametrize("P,low,high,bound", [(256, 0.38, 0.48, 1.45), (16, 0.38, 0.5, 1.6), (8, 0.24, 0.36, 1.5)])
+def test_reduce_blocks(P, low, high, bound):
+    N = 1 << 24
+    t0, t1 = _time(*[_reduce(N, [_uniform(N, int(N * m / P), r) for r in range(P)]) for m in (low, high)])
+    say(f"[cost] blocks P={P}: {t1:.1f} us, a little fewer entries {t0:.1f} us")
+    assert t1 < bound * t0
