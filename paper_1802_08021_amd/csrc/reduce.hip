@@ -437,10 +437,11 @@ hipError_t reduce_run(const ReducePlan& p, const StreamDesc* host_tab, uint32_t*
     // 2^25, us without and with: 2 ranks 0.25 294, 194; 16 ranks 0.5 340, 285 and
     // 2 688, 513; 32 ranks 0.1 77, 64 and 0.25 99, 152; 64 ranks 0.25 138, 115 and
     // 0.5 167, 191; 128 ranks 0.25 246, 129, 0.5 292, 250 and 1 335, 414; 256
-    // ranks 0.1 1168, 232 and 1 2332, 967.  Below 2^22 indices the launch shows
-    // (2^20, 64 ranks, 0.25: 22, 30).
+    // ranks 0.1 1168, 232 and 1 2332, 967.  Below 2^22 indices (2^20 above 128
+    // ranks) the launch shows (2^20, 64 ranks, 0.25: 22, 30; 2^18, 256 ranks, 0.25:
+    // 46, 62).
     const uint64_t most = pmax <= 16u ? 16u : (pmax <= 32u ? 1u : (pmax <= 64u ? 2u : (pmax <= 128u ? 4u : 16u)));  // eighths
-    const bool pairs = (p.N >= 1u << 22 || pmax > 128u) && 8u * p.sum_nnz <= most * p.N;
+    const bool pairs = p.N >= (pmax > 128u ? 1u << 20 : 1u << 22) && 8u * p.sum_nnz <= most * p.N;
     a.when = info ? kWhenNodes : (p.speculate_dense ? kWhenUnion : kWhenSparse);
     if (p.speculate_dense) {
         const bool with = info && !pairs;

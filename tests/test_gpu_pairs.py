@@ -1,5 +1,5 @@
-"""Node sizes counted from the indices alone (2^22 indices or more, or more
-than 128 ranks, where few indices have two entries; the other reduce tests
+"""Node sizes counted from the indices alone (2^22 indices or more, 2^20 above
+128 ranks, where few indices have two entries; the other reduce tests
 reach the tile pass's): every number of slots a wave, streams shared by
 several waves, several tiles a chunk, more indices held twice than a round of
 rows takes (shared supports), entries crowded into a part of the range, a range
@@ -29,9 +29,9 @@ CASES = [
     (64, 40_000_001, None, 20_000, "ragged", 0, 0.9),
     (100, N22, None, 5_000, "uniform", 4, 0.001),
     (128, N22 + 1, None, 300, "ragged", 0, "band"),
-    (129, 5_000, None, 9, "uniform", 0, 0.9),
-    (150, 300_001, (100_000, 290_001), 1_500, "crowded", 0, 0.01),
-    (256, 100_003, None, 500, "shared", 0, "band"),
+    (129, 1 << 20, None, 1_500, "uniform", 0, 0.9),
+    (150, 3_000_001, (100_000, 1_290_001), 1_500, "crowded", 0, 0.01),
+    (256, 1_100_003, None, 5_000, "shared", 0, "band"),
     (256, 1_000_003, None, 6_000, "uniform", 4, 0.001),
 ]
 
@@ -80,3 +80,9 @@ def test_pairs(P, N, rng_, k, shape, qbits, delta):
         if info:
             np.testing.assert_array_equal(to_np(c.node_nnz).astype(np.uint64), o["node_nnz"].astype(np.uint64))
             np.testing.assert_array_equal(to_np(c.node_dense).astype(np.uint8), o["node_dense"].astype(np.uint8))
+
+
+@pytest.mark.parametrize("P,N,k", [(128, N22 - 1, 900), (129, (1 << 20) - 1, 400)])
+def test_below(P, N, k):
+    """Just below the rule's sizes, by the tile pass."""
+    test_pairs(P, N, None, k, "uniform", 0, 0.001)
