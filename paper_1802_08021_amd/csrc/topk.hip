@@ -18,7 +18,8 @@
 // passes, a count pass and a write pass over its data.
 //
 // Where a unit would gather too much (more than kSlots / 4 selections expected),
-// the selection is bracketed instead: a larger and finer sample gives a window
+// a short row takes the histogram passes at once, and of a long one the
+// selection is bracketed: a larger and finer sample gives a window
 // of keys that holds K*, one pass counts each unit's keys above it and keeps
 // those inside it (a few per unit), histograms of these give K*, and a second
 // pass over the data writes the selection.  A row whose K* lies outside its
@@ -125,7 +126,16 @@ __device__ __forceinline__ void for_keys(const float* row, uint64_t lo, uint64_t
         }
         for (uint64_t e = hv + t; e < hi; e += nt) f(e, mag_key(row[e]));
     } else {
-        for (uint64_t e = lo + t; e < hi; e += nt) f(e, mag_key(row[e]));
+        // eight single loads in flight (8 rows of 20,001, 43 selected of each: 85 -> 58 us)
+        const uint64_t step = 8ull * nt, hb = lo + ((hi - lo) / step) * step;
+        for (uint64_t e = lo + t; e < hb; e += step) {
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = row[e + (uint64_t)nt * q];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) f(e + (uint64_t)nt * q, mag_key(v[q]));
+        }
+        for (uint64_t e = hb + t; e < hi; e += nt) f(e, mag_key(row[e]));
     }
 }
 
@@ -565,7 +575,7 @@ __global__ void __launch_bounds__(1024) k_win_sample(const float* x, uint64_t N,
         if (n.w) atomicAdd(&kw[i + 3u], n.w);
     }
     if (!last_of_row(kcnt, r, kTickSample, gridDim.x, &s_last)) return;
-    const double kf = (double)k * f, d = f < 1.0 ? 4.0 * sqrt(kf) + 16.0 : 0.0;  // (a short row is sampled whole)
+    const double kf = (double)k * f, d = 4.0 * sqrt(kf) + 16.0;
     const uint32_t t_lo = (uint32_t)ceil(kf + d), t_hi = kf > d ? (uint32_t)floor(kf - d) : 0u;
     if (tid < 2u) s_bin[tid] = tid ? kFine - 1u : 0u;  // (no such key: to the end of the range)
     // thread tid owns bins [lo, lo + 32), threads ordered from the top
@@ -943,6 +953,7 @@ __global__ void __launch_bounds__(256) k_count(const float* x, uint64_t N, uint3
                     }
                 }
             } else {
+#pragma unroll 8
                 for (uint64_t e = lo + lane; e < hi; e += 64) one(row[e]);
             }
             const uint32_t all = wave_scan(ge);  // (at most 4096 each)
@@ -1037,30 +1048,36 @@ __device__ void write_unit(const float* x, uint64_t N, uint64_t k, uint32_t U, u
         }
         return;
     }
-    for (uint64_t e0 = lo; e0 < hi; e0 += 64) {
-        const uint64_t e = e0 + lane;
-        const bool valid = e < hi;
-        const float v = valid ? row[e] : 0.0f;
-        const uint32_t key = mag_key(v);
-        const bool eq = valid && key == K;
-        const uint64_t beq_w = __ballot(eq);
-        const bool take_eq = eq && (eq_run + (uint64_t)__popcll(beq_w & lt)) < need;
-        const bool sel = (valid && key > K) || take_eq;
-        const uint64_t bsel = __ballot(sel);
-        if (sel) {
-            const uint32_t o = out_run + (uint32_t)__popcll(bsel & lt);
-            oi[o] = (uint32_t)e;
-            ov[o] = v;
-        }
-        if (res && valid) {
-            if (inplace) {
-                if (sel) res[e] = 0.0f;
-            } else {
-                res[e] = sel ? 0.0f : v;
+    for (uint64_t e8 = lo; e8 < hi; e8 += 512) {  // (eight loads in flight)
+        float v8[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v8[q] = e8 + 64u * q + lane < hi ? row[e8 + 64u * q + lane] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const uint64_t e = e8 + 64u * q + lane;
+            const bool valid = e < hi;
+            const float v = v8[q];
+            const uint32_t key = mag_key(v);
+            const bool eq = valid && key == K;
+            const uint64_t beq_w = __ballot(eq);
+            const bool take_eq = eq && (eq_run + (uint64_t)__popcll(beq_w & lt)) < need;
+            const bool sel = (valid && key > K) || take_eq;
+            const uint64_t bsel = __ballot(sel);
+            if (sel) {
+                const uint32_t o = out_run + (uint32_t)__popcll(bsel & lt);
+                oi[o] = (uint32_t)e;
+                ov[o] = v;
             }
+            if (res && valid) {
+                if (inplace) {
+                    if (sel) res[e] = 0.0f;
+                } else {
+                    res[e] = sel ? 0.0f : v;
+                }
+            }
+            eq_run += (uint64_t)__popcll(beq_w);
+            out_run += (uint32_t)__popcll(bsel);
         }
-        eq_run += (uint64_t)__popcll(beq_w);
-        out_run += (uint32_t)__popcll(bsel);
     }
 }
 
@@ -1155,12 +1172,20 @@ hipError_t topk_run(int P, const float* x, uint64_t N, uint64_t k, uint32_t* out
     }
     const TLayout l = tlayout(P, N, ws);
     // The expected selections per unit decide where a row starts: up to a
-    // quarter of what a unit gathers, with a gather (its entries, a few times the
-    // selections, are then the only ones read again); up to a quarter of
-    // the elements, with a window; above, where a window of the sample's accuracy
-    // could fill a unit's slots, with the passes over the data.
+    // quarter of what a unit gathers (of long rows a little more: 64 rows of 2^20,
+    // 9 a unit: 156 us, through the window 274), with a gather (its entries, a few
+    // times the selections, are then the only ones read again); up to a quarter of
+    // the elements, long rows with a window; above, where a window of the sample's
+    // accuracy could fill a unit's slots, and short rows with the passes over the
+    // data: a window costs each row 140 KB of histograms, the passes three more
+    // reads of it (41 a unit, us, window and passes: one row of 2^16 55, 43; of 2^20
+    // 61, 51; of 2^22 65, 89; 8 rows of 2^20 82, 62; 64 rows of 2^12 58, 35; of 2^18
+    // 128, 98; of 2^20 276, 309; 512 rows of 2^16 440, 169; 4096 of 2^12 648, 156).
     const double per_unit = (double)k * kUnit / (double)N;
-    const bool win = per_unit > kSlots / 4 && per_unit <= kUnit / 4, passes = per_unit > kUnit / 4;
+    const bool gather = per_unit <= (N >= 1u << 18 ? 9.25 : 8.0);
+    const bool wide = N >= 1u << 21 || (N >= 1u << 20 && (uint64_t)P * N >= 1u << 26);
+    const bool win = !gather && wide && per_unit <= kUnit / 4, passes = !gather && !win;
+    static_assert(kSlots == 32 && kUnit == 4096, "the lines above");
     const uint64_t ninit = (uint64_t)P * (win ? kWinWords : 2048u);
     hipLaunchKernelGGL(k_init, dim3((uint32_t)std::min<uint64_t>((ninit + 255) / 256, 1024)), dim3(256), 0, s, l.st,
                        (uint32_t)P, k, l.hist, l.overflow, l.kcnt, l.klist, win ? 1u : 0u, passes ? 1u : 0u);

@@ -124,3 +124,19 @@ def test_reduce_blocks(P, low, high, bound):
     t0, t1 = _time(*[_reduce(N, [_uniform(N, int(N * m / P), r) for r in range(P)]) for m in (low, high)])
     say(f"[cost] blocks P={P}: {t1:.1f} us, a little fewer entries {t0:.1f} us")
     assert t1 < bound * t0
+
+
+# Top-k of many short rows, ten times the entries against ten times fewer (which
+# come from one gather).  With a window of keys, whose histograms are larger than
+# the rows, 2.2, 1.06 and 1.8 times as long; with passes over the rows 0.54, 0.68
+# and 0.61 times.
+@pytest.mark.parametrize("P,N,bound", [(4096, 4096, 1.1), (64, 4096, 0.85), (512, 16384, 1.05)])
+def test_topk_short_rows(P, N, bound):
+    from paper_1802_08021_amd import sparcml as S
+    torch, dev = torch_dev()
+    g = torch.Generator(device=dev)
+    g.manual_seed(P)
+    x = torch.randn(P, N, generator=g, device=dev)
+    t0, t1 = _time(S.TopkCall(x, N // 1000).run, S.TopkCall(x, N // 100).run)
+    say(f"[cost] top-k of {P} x {N}: {t1:.1f} us, a tenth of the entries {t0:.1f} us")
+    assert t1 < bound * t0
