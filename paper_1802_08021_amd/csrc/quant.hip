@@ -238,17 +238,18 @@ __device__ __forceinline__ void quant_word(const QDesc& d, uint32_t r, uint64_t 
     }
 }
 
-// Each thread quantizes 32/bits consecutive elements into one word; with
-// 8-bit codes, where these are one 16-byte load, kWords words 256 apart whose
-// loads are in flight together.
-template <int BITS>
-constexpr int kWords = BITS == 8 ? 4 : 1;
+// Each thread quantizes 32/bits consecutive elements into W words, 256 apart,
+// whose loads are in flight together: four words of 8-bit codes, where one is a
+// single 16-byte load, beside dequantized copies; without the copies one word,
+// in four times as many workgroups (8 streams of 2^20 22.3 -> 20.3 us, 64 of 2^17
+// 22.7 -> 21.7).
+constexpr int kWords = 4;
 
-template <int BITS, int ARGS>
+template <int BITS, int ARGS, int W = 1>
 __global__ void __launch_bounds__(256) k_quantize(const QDesc* tab, Blob tb, const float* scales, uint32_t k0,
                                                   uint32_t k1)
 {
-    constexpr int EPT = 32 / BITS, W = kWords<BITS>;
+    constexpr int EPT = 32 / BITS;
     const uint32_t r = blockIdx.y;
     const QDesc d = qdesc<ARGS>(tab, tb, r);
     const uint64_t e0 = ((uint64_t)blockIdx.x * (256 * W) + threadIdx.x) * EPT;
@@ -318,15 +319,19 @@ struct QBDesc {
 };
 constexpr uint32_t kQBWords = sizeof(QBDesc) / 4;
 
+struct NoBlob {};  // (3 KB of arguments less to copy, about 1 us a launch)
+template <bool ARGS>
+using BucketTab = std::conditional_t<ARGS, Blob, NoBlob>;
+
 template <int BITS, int EPT, bool ARGS>
-__global__ void __launch_bounds__(256) k_quantize_buckets(const QBDesc* tab, Blob tb, float* scales, uint32_t B,
+__global__ void __launch_bounds__(256) k_quantize_buckets(const QBDesc* tab, BucketTab<ARGS> tb, float* scales, uint32_t B,
                                                           uint32_t k0, uint32_t k1)
 {
     constexpr uint32_t S = (1u << (BITS - 1)) - 1u;
     __shared__ double s_w[4];
     const uint32_t r = blockIdx.y;
     QBDesc d;
-    if (ARGS) {  // five words of 64 bits a stream
+    if constexpr (ARGS) {  // five words of 64 bits a stream
         const uint32_t* w = tb.words + kQBWords * r;
         auto u64 = [&](int i) { return (uint64_t)w[2 * i] | (uint64_t)w[2 * i + 1] << 32; };
         d.val = reinterpret_cast<const float*>(u64(0));
@@ -455,8 +460,8 @@ QLayout qlayout(int P, uint64_t max_n, void* ws)
 }
 
 template <int BITS, bool ARGS>
-void launch_buckets(dim3 grid, int ept, hipStream_t s, const QBDesc* tab, const Blob& tb, float* scales, uint32_t B,
-                    uint32_t k0, uint32_t k1)
+void launch_buckets(dim3 grid, int ept, hipStream_t s, const QBDesc* tab, const BucketTab<ARGS>& tb, float* scales,
+                    uint32_t B, uint32_t k0, uint32_t k1)
 {
     const auto k = ept == 4    ? k_quantize_buckets<BITS, 4, ARGS>
                    : ept == 8  ? k_quantize_buckets<BITS, 8, ARGS>
@@ -503,14 +508,14 @@ hipError_t quant_buckets_run(int P, const float* const* vals, const uint64_t* n,
     const dim3 grid((uint32_t)((max_n + per_block - 1) / per_block), P);
     const uint32_t k0 = (uint32_t)(seed & 0xFFFFFFFFu), k1 = (uint32_t)(seed >> 32);
     timer_begin(kTQuantCodes, s);
-    auto run = [&](auto args) {
+    auto run = [&](auto args, const auto& t) {
         constexpr bool A = decltype(args)::value;
-        if (bits == 2) launch_buckets<2, A>(grid, ept, s, tab, tb, out_scale, bucket, k0, k1);
-        else if (bits == 4) launch_buckets<4, A>(grid, ept, s, tab, tb, out_scale, bucket, k0, k1);
-        else launch_buckets<8, A>(grid, ept, s, tab, tb, out_scale, bucket, k0, k1);
+        if (bits == 2) launch_buckets<2, A>(grid, ept, s, tab, t, out_scale, bucket, k0, k1);
+        else if (bits == 4) launch_buckets<4, A>(grid, ept, s, tab, t, out_scale, bucket, k0, k1);
+        else launch_buckets<8, A>(grid, ept, s, tab, t, out_scale, bucket, k0, k1);
     };
-    if (tb.nwords) run(std::true_type{});
-    else run(std::false_type{});
+    if (tb.nwords) run(std::true_type{}, tb);
+    else run(std::false_type{}, NoBlob{});
     timer_end(kTQuantCodes, s);
     return hipGetLastError();
 }
@@ -555,7 +560,9 @@ hipError_t quant_run(int P, const float* const* vals, const uint64_t* n, int bit
     }
 
     const uint32_t k0 = (uint32_t)(seed & 0xFFFFFFFFu), k1 = (uint32_t)(seed >> 32);
-    auto pick = [&](auto table, auto six, auto eight) { return !tb.nwords ? table : (args == 6u ? six : eight); };
+    auto pick = [&](auto table, decltype(table) six, decltype(table) eight) {
+        return !tb.nwords ? table : (args == 6u ? six : eight);
+    };
     if (max_n > 0 && max_n <= kSmallQ) {  // short streams: norm and codes in one launch
         timer_begin(kTQuantCodes, s);
         const auto small = bits == 2 ? pick(k_quant_small<2, 0>, k_quant_small<2, 6>, k_quant_small<2, 8>)
@@ -576,11 +583,13 @@ hipError_t quant_run(int P, const float* const* vals, const uint64_t* n, int bit
                            l.count[lv - 1], l.part[lv], l.count[lv], lv == l.levels ? out_scale : nullptr);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (max_n == 0) return hipSuccess;
-    const uint64_t per_block = 256ull * (32 / bits) * (bits == 8 ? kWords<8> : bits == 4 ? kWords<4> : kWords<2>);
+    const int words = bits == 8 && out_deq ? kWords : 1;
+    const uint64_t per_block = 256ull * (32 / bits) * words;
     const dim3 grid((uint32_t)((max_n + per_block - 1) / per_block), P);
     const auto codes = bits == 2 ? pick(k_quantize<2, 0>, k_quantize<2, 6>, k_quantize<2, 8>)
                        : bits == 4 ? pick(k_quantize<4, 0>, k_quantize<4, 6>, k_quantize<4, 8>)
-                                   : pick(k_quantize<8, 0>, k_quantize<8, 6>, k_quantize<8, 8>);
+                       : out_deq   ? pick(k_quantize<8, 0, kWords>, nullptr, k_quantize<8, 8, kWords>)
+                                   : pick(k_quantize<8, 0>, k_quantize<8, 6>, nullptr);
     timer_begin(kTQuantCodes, s);
     hipLaunchKernelGGL(codes, grid, dim3(256), 0, s, l.tab, tb, out_scale, k0, k1);
     timer_end(kTQuantCodes, s);
