@@ -24,7 +24,7 @@ namespace sparcml {
 namespace {
 
 constexpr uint32_t kPairTile = 1u << 17;          // indices a tile at most
-constexpr uint32_t kPairRowWords = 29696;         // rows: 116 KB beside 32 KB of bits
+constexpr uint32_t kPairRowWords = 25600;         // rows: 100 KB beside 32 KB of bits and 16 KB of counts
 constexpr uint32_t pair_rows(uint32_t mw) { return kPairRowWords / mw; }
 
 // SL slots a wave (16 SL tree slots); with SL = 1 a slot's entries are shared by
@@ -37,7 +37,15 @@ __global__ void __launch_bounds__(1024, 4) k_pairs(AccArgs a)
     constexpr uint32_t kNone = 0xFFFFFFFFu;
     __shared__ __align__(16) uint32_t s_once[W + 64], s_twice[W];  // (64 more for lanes without an entry)
     __shared__ __align__(16) uint32_t s_row[kPairRowWords];
-    __shared__ uint32_t s_E[16 * SL], s_tot[16];
+    // Counts of the nodes, sixteen copies: lanes that add to one node at once
+    // (runs that all ranks share) would wait for each other, as would lanes whose
+    // bits lie in one word: consecutive indices take consecutive words.  (16 ranks
+    // that share a run, 2^22: 193 -> 160 us a call.)
+    constexpr uint32_t EW = 16u * SL + 1u;
+    __shared__ uint32_t s_E[16u * EW], s_tot[16];
+    static_assert(W == 4096u && kPairTile == 32u * W, "an index's word its low 12 bits, its bit the five above");
+    auto word = [](uint32_t j) -> uint32_t { return j & (W - 1u); };
+    auto bit = [](uint32_t j) -> uint32_t { return j >> 12 & 31u; };
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t P = a.P, T = a.T, chunk = blockIdx.x;
@@ -80,7 +88,7 @@ __global__ void __launch_bounds__(1024, 4) k_pairs(AccArgs a)
         upto = max(upto, pos);
     }
     for (uint32_t i = tid; i < W; i += NT) s_once[i] = s_twice[i] = 0u;
-    for (uint32_t i = tid; i < 16u * SL; i += NT) s_E[i] = 0u;
+    for (uint32_t i = tid; i < 16u * EW; i += NT) s_E[i] = 0u;
     __syncthreads();
 
     const uint32_t cw = (uint32_t)(chi - clo);
@@ -125,10 +133,10 @@ __global__ void __launch_bounds__(1024, 4) k_pairs(AccArgs a)
             uint32_t old[GS * U];
 #pragma unroll
             for (int k = 0; k < GS * U; ++k)
-                old[k] = atomicOr(&s_once[j[k] != kNone ? j[k] >> 5 : W + lane], 1u << (j[k] & 31u));
+                old[k] = atomicOr(&s_once[j[k] != kNone ? word(j[k]) : W + lane], 1u << bit(j[k]));
 #pragma unroll
             for (int k = 0; k < GS * U; ++k)
-                if (j[k] != kNone && (old[k] >> (j[k] & 31u) & 1u)) atomicOr(&s_twice[j[k] >> 5], 1u << (j[k] & 31u));
+                if (j[k] != kNone && (old[k] >> bit(j[k]) & 1u)) atomicOr(&s_twice[word(j[k])], 1u << bit(j[k]));
         });
         __syncthreads();
         // Numbers: s_once takes the first of each word.
@@ -155,13 +163,13 @@ __global__ void __launch_bounds__(1024, 4) k_pairs(AccArgs a)
                 uint32_t tw[GS * U], id[GS * U];
 #pragma unroll
                 for (int k = 0; k < GS * U; ++k) {
-                    const uint32_t w = j[k] != kNone ? j[k] >> 5 : 0u;
+                    const uint32_t w = j[k] != kNone ? word(j[k]) : 0u;
                     tw[k] = s_twice[w];
                     id[k] = s_once[w];
                 }
 #pragma unroll
                 for (int k = 0; k < GS * U; ++k) {
-                    const uint32_t b = 1u << (j[k] & 31u), i = id[k] + (uint32_t)__popc(tw[k] & (b - 1u)) - base;
+                    const uint32_t b = 1u << bit(j[k]), i = id[k] + (uint32_t)__popc(tw[k] & (b - 1u)) - base;
                     const uint32_t rank = r + (uint32_t)(k / U);
                     if (j[k] != kNone && (tw[k] & b) && i < nr) atomicOr(&s_row[i * MW + (rank >> 5)], 1u << (rank & 31u));
                 }
@@ -176,7 +184,7 @@ __global__ void __launch_bounds__(1024, 4) k_pairs(AccArgs a)
                         const uint32_t r = w * 32u + (uint32_t)__builtin_ctz(m);
                         if (pred != kNone) {
                             const uint32_t h = 31u - (uint32_t)__clz(pred ^ r);
-                            atomicAdd(&s_E[P - (P >> h) + (r >> (h + 1u))], 1u);
+                            atomicAdd(&s_E[(lane & 15u) * EW + P - (P >> h) + (r >> (h + 1u))], 1u);
                         }
                         pred = r;
                     }
@@ -190,8 +198,11 @@ __global__ void __launch_bounds__(1024, 4) k_pairs(AccArgs a)
     }
     const uint32_t all = block_sum(ne, s_tot);
     if (tid == 0u && a.when != kWhenUnion) a.chunk_ne[chunk] = all;
-    for (uint32_t i = tid; i + 1u < P; i += NT)
-        if (s_E[i]) atomicAdd(&a.node_cnt[i], s_E[i]);
+    for (uint32_t i = tid; i + 1u < P; i += NT) {
+        uint32_t n = 0u;
+        for (uint32_t c = 0; c < 16u; ++c) n += s_E[c * EW + i];
+        if (n) atomicAdd(&a.node_cnt[i], n);
+    }
 }
 
 }  // namespace
