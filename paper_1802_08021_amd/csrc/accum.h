@@ -26,8 +26,10 @@
 //
 // What bounds it: instruction issue (about fifty a slot and tile, one in four
 // to five cycles a SIMD) and, near it, the LDS pipe (a scattered access of a
-// wave takes 7 cycles, and an entry needs two); memory waits are hidden by
-// requesting a tile's windows during the one before.  The walk it replaced
+// wave takes 7 cycles, and an entry needs two).  Memory waits are hidden by
+// requesting a tile's windows during the one before, except where a chunk is a
+// tile or two (its first windows), where windows are read on (below), and, above
+// 128 slots, where heavy indices ask for entries that were not kept.  The walk it replaced
 // ranked every entry among its tile's and merged them index by index.  Whole
 // calls, before and after: 128 ranks at 1% of 2^27, 4-bit codes: 1183 -> 790
 // us; 64 ranks, zipf supports, 2^26: 297 -> 211 us (heavy indices: half of
@@ -130,12 +132,8 @@ namespace {
 
 // Pointers that live in memory are generic unless marked: generic (FLAT)
 // loads also count against the LDS wait counter and would serialize LDS work
-// behind every HBM access.  What a wave reads alike goes through the constant
-// address space, so that it becomes a scalar load.
+// behind every HBM access.
 typedef const uint32_t __attribute__((address_space(1))) g_u32;
-typedef const uint8_t __attribute__((address_space(1))) g_u8;
-typedef const StreamDesc __attribute__((address_space(4))) c_desc;
-typedef const uint32_t __attribute__((address_space(4))) c_u32;
 
 // Mask of the active lanes where a < b (unsigned), where v is neither zero:
 // one compare each.

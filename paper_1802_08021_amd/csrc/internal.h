@@ -146,7 +146,7 @@ hipError_t reduce_run(const ReducePlan& p, const StreamDesc* host_tab, uint32_t*
 
 // Small-data path: at most 8 slots holding at most thr entries together (so
 // every node stays sparse), few enough that one workgroup's merge tree is
-// faster than the tile pipeline.
+// faster than the tile pass.
 bool merge_small_fits(uint32_t PT, uint64_t sum_nnz, uint64_t thr);
 // The whole tree in one launch: root to out_idx / out_val, node sizes (in
 // the order of reduce_run), header to hdr and, if not NULL, result.
@@ -155,7 +155,10 @@ hipError_t merge_small_run(uint32_t PT, uint32_t L, uint32_t qbits, uint32_t nfo
                            ReduceResult* hdr, ReduceResult* result, hipStream_t s);
 
 // Segmented merge path: at most 64 slots, every node sparse, at most
-// kSegMaxEntries entries; the range cut into nseg segments of segw indices
+// kSegMaxEntries entries (a limit set against an earlier tile pass: today's is
+// faster on short vectors -- 16, 32, 64 ranks, 2^18 entries, merge and tiles: of
+// 2^20 25 and 19, 28 and 18, 32 and 19 us, of 2^23 26 and 23, 28 and 24, 32 and 25 --
+// and slower on long ones, 2^26: 25 and 67, 28 and 74, 32 and 89); the range cut into nseg segments of segw indices
 // (merge_seg_shape), each merged by one workgroup.
 constexpr uint64_t kSegEntries = 2048;                     // expected entries per segment
 constexpr uint32_t kSegMax = 1024;                         // segments at most

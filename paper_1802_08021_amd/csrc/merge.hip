@@ -28,8 +28,8 @@
 // Two kernels use it.  k_merge_small: one workgroup takes the whole range
 // (one launch, the slot table in the kernel arguments).  A level costs about
 // 4.5 us of dependent LDS round trips and barriers even when it holds few
-// entries, while the tile pipeline costs about 23-30 us of launches for any
-// small input (measured on MI355X, P = 4..32, 256..16384 entries), so it is
+// entries, while the tile pass costs about 15-20 us of launches for any small
+// input (2^20 indices; measured on MI355X, P = 4..32, 256..16384 entries), so it is
 // taken for at most 8 slots with at most 16384 / 8192 / 1024 entries for
 // one, two, three levels.  k_merge_seg: the range is cut into segments of
 // equal width (about kSegEntries expected entries each, at least kSegMin

@@ -27,8 +27,8 @@
 // histogram passes over its data.  Every path is exact: the sample only
 // decides how much data is read.
 //
-// One row of 23.5 M with k = 1% and a new residual: 449 us by the histogram
-// passes from 64 workgroups, 112 us by the window.
+// One row of 23.5 M with k = 1% and a new residual: a call takes 449 us by the
+// histogram passes from 64 workgroups, 126 us by the window.
 #include "internal.h"
 
 #include <algorithm>
@@ -285,7 +285,6 @@ __global__ void __launch_bounds__(256) k_estimate(RankState* st, uint32_t* hist,
     __shared__ uint32_t s_w[4];
     __shared__ uint32_t s_bin;
     const uint32_t r = blockIdx.x, tid = threadIdx.x;
-    if (st[r].exact != 0u) return;  // the row starts from the exact bin
     uint32_t* h = hist + (uint64_t)r * 2048;
     const double kf = (double)k * f;
     const uint64_t t = (uint64_t)ceil(kf + 4.0 * sqrt(kf) + 16.0);
@@ -844,10 +843,6 @@ __global__ void __launch_bounds__(256) k_win_part(const float* x, uint64_t N, ui
     }
 }
 
-// Per unit: entries with key > K* (low half; at most 4096) and key == K*.  A wave takes kUPW
-// consecutive units: from the gathered entries on a settled row (all loads
-// in flight together), or the window's keys and the count above it, from the
-// data on a row refined over it.
 constexpr uint32_t kUPW = 8;  // units per wave in the count and write kernels
 
 // Unit offsets: equal keys are taken in index order until `need` of them.
@@ -916,6 +911,10 @@ __global__ void __launch_bounds__(1024) k_unit_scan(uint32_t U, const RankState*
     }
 }
 
+// Per unit: entries with key > K* (low half; at most 4096) and key == K*.  A
+// wave takes kUPW consecutive units: from the gathered entries on a settled row
+// (all loads in flight together), or the window's keys and the count above it,
+// from the data on a row refined over it.
 __global__ void __launch_bounds__(256) k_count(const float* x, uint64_t N, uint32_t U, const RankState* st,
                                                 const uint2* cand, const uint32_t* ccnt, const uint32_t* cgt, uint32_t* cnt)
 {

@@ -1,6 +1,6 @@
 """Seeded random sweeps against the oracle.  The sparse reduce: across the
 paths the library picks by size (one-workgroup merge tree, segmented merge
-tree, tile pipeline with a sparse or a dense root, deferred tiles) and
+tree, tile pass with a sparse or a dense root, crowded tiles) and
 across what the other tests fix one at a time: rank counts that are not
 powers of two, QSGD codes of every width, the range entry point, and index
 sets that are uniform, clustered (heavy overlap between ranks) or runs of

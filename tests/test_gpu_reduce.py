@@ -4,7 +4,7 @@ Bit-exact: root representation, nnz, indices, per-node switch decisions and
 union sizes.  Values: within 1e-6 rel / 1e-7 abs, and bitwise (the kernels
 use the oracle's association).  Sizes span several tiles with a ragged
 tail; edge cases cover empty streams, a single rank, all-dense and
-all-sparse thresholds, overfull tiles (the slow path) and a sparse root
+all-sparse thresholds, crowded tiles (windows read on) and a sparse root
 reached after a dense guess."""
 import numpy as np
 import pytest
@@ -91,7 +91,7 @@ def test_thresholds_extremes_and_boundary():
     check([a, b], [inputs.normal(rng, 100), inputs.normal(rng, 100)], 1000, 0.199, "sum == thr+1")
 
 
-def test_overfull_tiles_take_the_slow_path():
+def test_crowded_tiles():
     rng = np.random.default_rng(5)
     N = 40000
     # dense-ish ranks: > 64 entries of one rank in a tile
@@ -100,7 +100,7 @@ def test_overfull_tiles_take_the_slow_path():
     val[0] = inputs.normal(rng, idx[0].size)
     check(idx, val, N, 0.3, "dense-ish ranks")
     check(idx, val, N, 100.0, "dense-ish ranks, all sparse")
-    # every rank clustered in one region: tile total above the fast-path cap
+    # every rank clustered in one region
     P = 128
     idx = [np.sort(rng.choice(3000, 60, replace=False)).astype(np.uint32) for _ in range(P)]
     val = [inputs.normal(rng, 60) for _ in range(P)]

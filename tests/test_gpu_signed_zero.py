@@ -4,8 +4,8 @@ A stream value may be -0.0.  The oracle's sparse sums keep the sign of zero
 as fp32 addition gives it (-0 + -0 = -0, -0 + +0 = +0, a lone -0 stays
 -0), and its dense nodes start from +0.0, so a dense value is never -0.0.
 These cases put -0.0 (and +0.0) at indices held by one, two, three and
-more ranks, into sparse roots, dense roots, a range, tiles that take the
-slow pass, the concatenation (sparse and dense results) and top-k rows
+more ranks, into sparse roots, dense roots, a range, tiles whose windows
+are read on, the concatenation (sparse and dense results) and top-k rows
 whose zeros of both signs tie for the last selected places."""
 import numpy as np
 import pytest
@@ -85,12 +85,12 @@ def test_reduce_counts_of_ranks_per_index():
     check(idx, val, N, 1e-9, "ranks per index, dense")
 
 
-def test_reduce_range_and_slow_tiles():
+def test_reduce_range_and_crowded_tiles():
     rng = np.random.default_rng(910)
     N = 200003
     lo, hi = 70001, 170003
     P = 256
-    # dense per-rank streams in a narrow window overflow the fast pass
+    # a run that every rank holds: many windows a tile, every index heavy
     idx, val = [], []
     for r in range(P):
         a = np.arange(lo + 100, lo + 100 + 3000, dtype=np.uint32)
@@ -98,8 +98,8 @@ def test_reduce_range_and_slow_tiles():
         v[rng.random(a.size) < 0.6] = NZ
         idx.append(a)
         val.append(v)
-    check(idx, val, N, 50.0, "overfull tiles, sparse root", rng_=(lo, hi))
-    check(idx, val, N, 1e-6, "overfull tiles, dense root", rng_=(lo, hi))
+    check(idx, val, N, 50.0, "crowded tiles, sparse root", rng_=(lo, hi))
+    check(idx, val, N, 1e-6, "crowded tiles, dense root", rng_=(lo, hi))
     idx, val = zero_streams(rng, 32, hi - lo, 3000)
     idx = [(a.astype(np.uint64) + lo).astype(np.uint32) for a in idx]
     check(idx, val, N, 0.5, "range, sparse root", rng_=(lo, hi))
