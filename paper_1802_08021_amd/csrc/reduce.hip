@@ -91,7 +91,8 @@ __device__ __forceinline__ StreamDesc arg_desc(const DescArgs& tb, uint32_t r)
 // When the descriptors travel in the arguments this launch also stores them
 // to `tab` for the later passes, and reads its own from the arguments.
 constexpr uint32_t kPartSamples = 1024;
-__global__ void __launch_bounds__(256) k_partition(StreamDesc* tab, DescArgs tb, uint32_t* off, uint32_t nchunks,
+constexpr uint32_t kPartThreads = 256;
+__global__ void __launch_bounds__(kPartThreads) k_partition(StreamDesc* tab, DescArgs tb, uint32_t* off, uint32_t nchunks,
                                                    uint64_t chunk_coords, uint64_t lo, uint64_t N, uint32_t* zero,
                                                    uint32_t nzero, ReduceResult* hdr, ReduceResult* res,
                                                    uint32_t qbits, uint32_t* pad, uint32_t* none, uint32_t* odd)
@@ -148,13 +149,15 @@ __global__ void __launch_bounds__(256) k_partition(StreamDesc* tab, DescArgs tb,
         s_off[c] = res;
     }
     __syncthreads();
+    static_assert(kPartThreads == 256u, "four waves, four bytes");
     // Whether a chunk holds far more of the stream than the others (never, of
     // an evenly drawn one: half of the mean and 64 are six deviations or more)
     const uint32_t most = nnz / nchunks + nnz / nchunks / 2u + 64u;
     bool far = false;
     for (uint32_t c = tid; c < nchunks; c += blockDim.x) far |= s_off[c + 1u] > s_off[c] && s_off[c + 1u] - s_off[c] > most;
-    const int any = __syncthreads_or(far);
-    if (tid == 0) odd[r] = any ? 1u : 0u;
+    // (a byte of the stream's word a wave: no further barrier)
+    const bool any = __ballot(far) != 0u;
+    if ((tid & 63u) == 0u) reinterpret_cast<uint8_t*>(odd + r)[tid >> 6] = any ? 1 : 0;
 }
 
 // Per-segment start offsets of every stream by one pass over its entries,
@@ -364,7 +367,7 @@ hipError_t reduce_run(const ReducePlan& p, const StreamDesc* host_tab, uint32_t*
                            tb, l.off, p.nseg, p.segw, p.lo, l.zero, nzero);
     } else {
         const uint32_t nzero = p.P;
-        hipLaunchKernelGGL(k_partition, dim3(p.P), dim3(256), 0, s, l.tab, tb, l.off, p.nchunks, p.chunk, p.lo,
+        hipLaunchKernelGGL(k_partition, dim3(p.P), dim3(kPartThreads), 0, s, l.tab, tb, l.off, p.nchunks, p.chunk, p.lo,
                            p.N, l.zero, nzero, l.hdr, dev_result, p.qbits, l.pad, l.none, l.odd);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
