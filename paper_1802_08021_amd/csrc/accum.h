@@ -24,16 +24,18 @@
 // (LDS float atomics would need neither the fields nor the second step, but
 // ds_add_f32 takes 193 cycles a wave here against 7.4 for an integer one.)
 //
-// What bounds it: instruction issue (about fifty a slot and tile, one in four
-// to five cycles a SIMD) and, near it, the LDS pipe (a scattered access of a
-// wave takes 7 cycles, and an entry needs two).  Memory waits are hidden by
-// requesting a tile's windows during the one before, except where a chunk is a
+// What bounds it: no one thing.  At 128 ranks, 1% of 2^27, a wave takes 300
+// vector, 64 scalar and 25 LDS instructions a tile (about fifty a slot) and
+// waits 55% of its cycles, for the LDS pipe (a scattered access of a wave takes
+// 7 cycles, an entry needs two; half of its cycles are conflicts), the three
+// barriers of a tile and memory.  A tile's windows are requested during the one
+// before, except where a chunk is a
 // tile or two (its first windows), where windows are read on (below), and, above
 // 128 slots, where heavy indices ask for entries that were not kept.  The walk it replaced
 // ranked every entry among its tile's and merged them index by index.  Whole
-// calls, before and after: 128 ranks at 1% of 2^27, 4-bit codes: 1183 -> 790
-// us; 64 ranks, zipf supports, 2^26: 297 -> 211 us (heavy indices: half of
-// the pass); 24 ragged ranks, sparse root of 5e7: 333 -> 104 us; 128 ranks
+// calls, before and after: 128 ranks at 1% of 2^27, 4-bit codes: 1186 -> 810
+// us; 64 ranks, zipf supports, 2^26: 298 -> 214 us (heavy indices: half of
+// the pass); 24 ragged ranks, sparse root of 5e7: 333 -> 105 us; 128 ranks
 // that share one support: 3.9 ms -> 0.17 ms.
 //
 // Clusters: where more of a stream than its window ends in a tile, the wave
